@@ -33,7 +33,7 @@ HBM_PEAK_GBS = 8000.0
 
 
 # phase -> (kernel name as in a kernel trace, marker comment that opens its
-# source block in kernels.hip); a phase of several kernels names the one
+# source block in kernels.hip, None for a kernel of another file); a phase of several kernels names the one
 # that dominates it.  The roofline object describes, among the phases that
 # are a single kernel launch (the others hold several launches, and their
 # event-timed spans include waits for the other stream), the one with the
@@ -44,15 +44,14 @@ PHASE_KERNEL = {
     "extension": ("k_extension", "// Extension of one cut leaf per work-group"),
     "p2m_up": ("k_up", "// Upward pass without the level-by-level chain."),
     "m2l": ("k_m2l_lanes", "// M2L: one lane per list-2 entry"),
-    "p2l": ("k_tgemm", "// Table GEMMs with 64-entry tiles"),
-    "m2p": ("k_tgemm", "// Table GEMMs with 64-entry tiles"),
+    "p2l": ("k_p2l", None),
+    "m2p": ("k_tgemm", "// Batched table GEMMs on the FP64 matrix cores"),
     "down": ("k_down", "// Downward pass without the level-by-level chain"),
-    "near_lowrank": ("k_near_lr", "// Near field in low-rank form"),
-    "near_dense": ("k_tgemm", "// Table GEMMs with 64-entry tiles"),
+    "near_lowrank": ("k_near_sym", None),  # the whole FP64 near field of the pair path
     "far": ("k_far", "// Far field and the near-field reduction"),
 }
 # the same phases on the target-stationary path (FP64, K = 16)
-PHASE_KERNEL_TS = dict(PHASE_KERNEL, near_lowrank=("k_tgemm", "// Table GEMMs with 64-entry tiles"),
+PHASE_KERNEL_TS = dict(PHASE_KERNEL, near_lowrank=("k_tgemm", "// Batched table GEMMs on the FP64 matrix cores"),
                        near_dense=("k_near_ts", None))
 
 
@@ -76,7 +75,7 @@ def algorithmic_work(case, precision="fp64"):
     ptr, src, cfg = plan.lists(1)
     counts = np.bincount(cfg, minlength=33)
     rk = ctx.debug_table(22, 0, 66)
-    lrR, rank = rk[:33].astype(int), rk[33:].astype(int)
+    rank = rk[33:].astype(int)
     # pairs (box, leaf below it) of the direct upward/downward passes
     lev = np.asarray(case["tree"]["level"])
     n_pairs_ud = int(np.maximum(lev - 2, 0).sum())
@@ -113,24 +112,34 @@ def algorithmic_work(case, precision="fp64"):
         # the far-field kernel: M2P values of list 3, the near sums, L2P; V written
         work["far"] = (8.0 * P * n * L + n * N3, 8.0 * n * N3 + 16.0 * L * n + 16.0 * L * P, "caller")
     else:
-        lr = lrR > 0
-        n_lr, n_dense = int(counts[lr].sum()), int(counts[~lr].sum())
-        work["near_lowrank"] = (float((counts * 4.0 * n * rank)[lr].sum()),
-                                8.0 * (L * n + n * n_lr) + 8.0 * 2 * n * 64 * int(lr.sum()), "side")
-        work["near_dense"] = (2.0 * n * n * n_dense, 8.0 * (L * n + n * n_dense) + 8.0 * n * n * int((~lr).sum()),
-                              "side")
-        work["far"] = (8.0 * P * n * L + n * (st["n_list1"] + N3),
-                       8.0 * n * (st["n_list1"] + N3) + 8.0 * L * n + 16.0 * L * P, "caller")
+        # per source leaf: its 4E = n - (K-4)^2 exterior moments; per target
+        # with same-level sources: per folded parity n/4 rows from n/4 own
+        # values and 8E moments of the neighbours (reflected ones combined);
+        # per pair of different levels: n values from 4E moments
+        E4 = n - (K - 4) ** 2
+        same = cfg < 9
+        tgt = np.repeat(np.arange(L), np.diff(ptr))
+        n_src, n_tgt = int(counts[4]), int(np.unique(tgt[same]).size)
+        n_pair = int((~same).sum())
+        work["near_lowrank"] = (2.0 * n * ((n / 4 + 2 * E4) * n_tgt + E4 * n_pair),
+                                8.0 * (n + E4) * n_src + 8.0 * n * (n_tgt + n_pair), "side")
+        work["p2m_up"] = (2.0 * n * (E4 + 2 * P) / 4 * n_src + 8.0 * P * P / 2 * n_pairs_ud,
+                          8.0 * (n + E4) * n_src + 16.0 * B * P, "caller")
+        work["p2l"] = (4.0 * P * E4 * N4, 8.0 * E4 * n_src + 16.0 * N4 * P, "side")
+        work["far"] = (8.0 * P * n * L + n * (n_tgt + n_pair + N3),
+                       8.0 * n * (n_tgt + n_pair + N3) + 8.0 * L * n + 16.0 * L * P, "caller")
     return work, ts
 
 
 def kernel_digest(marker):
     """Digest of a kernel's source: the block of kernels.hip from its opening
-    comment to the next separator line, or (marker None) all of near.hip."""
+    comment to the next separator line, or (marker None) the near field's
+    files."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_2211_14537_amd", "csrc")
     if marker is None:
-        return hashlib.sha256(open(os.path.join(csrc, "near.hip")).read().encode()).hexdigest()[:16]
+        text = "".join(open(os.path.join(csrc, f)).read() for f in ("near_sym.hip", "near.hip"))
+        return hashlib.sha256(text.encode()).hexdigest()[:16]
     src = open(os.path.join(csrc, "kernels.hip")).read()
     i = src.find(marker)
     if i < 0:
@@ -335,14 +344,14 @@ def bench_batch(args, dev):
     ext = {"batch_ms_per_rhs": ph_b["extension"] / nrhs, "single_ms": ph_1["extension"],
            "speedup": ph_1["extension"] * nrhs / max(ph_b["extension"], 1e-12),
            "batch_phases_ms": {k: v for k, v in ph_b.items() if k != "count"}}
-    # roofline of the low-rank near-field kernel in the batch: its
+    # roofline of the near-field kernel in the batch: its
     # algorithmic flops for every right-hand side over its event time
     base = dict(cfg=cfg, K=cfg["K"], p=cfg["p"], ctx=ctx, tree=tr, plan=plan,
                 interior=int(np.asarray(tr["mask"]).sum()))
     work, _ = algorithmic_work(base, "pairs")
     fl_nl = nrhs * work["near_lowrank"][0]
     t_nl = 1e-3 * ph_b["near_lowrank"]
-    roof = {"bound": "mfma", "kernel": "k_near_lr", "phase": "near_lowrank", "achieved": fl_nl / t_nl / 1e12,
+    roof = {"bound": "mfma", "kernel": "k_near_sym", "phase": "near_lowrank", "achieved": fl_nl / t_nl / 1e12,
             "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": fl_nl / t_nl / 1e12 / FP64_PEAK_TFLOPS,
             "traffic": None, "kernel_ms": 1e3 * t_nl, "algorithmic_flops": fl_nl}
     # the first and the last right-hand side against the oracle (as the

@@ -684,6 +684,12 @@ int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64
       size = (int64_t)v.size();
       break;
     }
+    case 29: case 30: case 31: case 32: {  // exterior moments (build_moments)
+      const std::vector<double>* v[] = {&T.mom_V, &T.mom_T, &T.sym_T, &T.pair_T};
+      src = v[which - 29]->data();
+      size = (int64_t)v[which - 29]->size();
+      break;
+    }
     case 23:
       if (index < 0 || index >= vfx::kP2LSlots) break;
       src = T.m2p_gemm.data() + (size_t)index * T.p2l_rows * n;

@@ -553,145 +553,17 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
 }
 
 // -------------------------------------------------------------------------
-// Batched table GEMMs on the FP64 matrix cores (near field, P2L, P2M, M2P)
-// for contraction lengths that are not a multiple of 32 (K = 4 and 12, whose
-// K^2 is 16 and 144); the others run on k_tgemm below, which has a deeper
-// pipeline.  Entries (pairs) are grouped by table configuration c; a work-group takes a
-// tile of <= TE entries (64 or 16) of one configuration and a block of MTB
-// row tiles (16 table rows each) and computes, for every entry e,
-//   Y[e][row] = sum_k A_c[k][row] X[src(e)][k]
-// (the table applied to the source leaf's K^2 values).
+// Batched table GEMMs on the FP64 matrix cores (M2P, the factor products of
+// the target-stationary near field): entries (pairs) are grouped by table
+// configuration c, and every entry e of a tile gets
+//   Y[e][row] = sum_k A_c[k][row] X[src(e)][k].
 //   A: [c][k][row], R = 16*MT rows (rows fastest, MT a multiple of MTB);
 //   X: [src][k] with row stride ldx, values k >= kx taken as zero (M2P reads
 //   the 2P coefficients of a multipole); Y: [e][row].
-// The K dimension is processed in blocks of 16 with both operands staged in
-// double-buffered LDS: the global loads of block kb+1 are in flight while the
-// waves run their MFMAs on block kb.  With TE = 64, wave w owns entries
-// 16w..16w+15 and every row tile of the block; with TE = 16 the waves share
-// the 16 entries and split the row tiles (w, w+4).  Row-tile counts are
-// compile-time, so the MFMA sequence has no per-tile branches.  MFMA
-// operands: A = entry data (16 entries x 4 k), B = table (4 k x 16 rows), so
-// each output tile is (entries x rows) and the stores of a 16-lane group are
-// 128 contiguous bytes.
 // v_mfma_f64_16x16x4f64: lane l holds A[l%16][l/16], B[l/16][l%16] and the
 // outputs D[(l/16) + 4r][l%16], r = 0..3 (lane layout checked on gfx950).
-// EPI = 1 (P2M): Y is the multipole array; rows < 2P of entry e (a leaf) are
-// scaled by h^2 of that leaf and stored as its (p+1) complex coefficients.
-template <int KD, int EPI, int TE, int MTB>
-__global__ void __launch_bounds__(256) k_gemm(int nitems, int MT, const int* __restrict__ t_cfg,
-                                              const int* __restrict__ t_first,
-                                              const int* __restrict__ t_count, const int* __restrict__ src,
-                                              const double* __restrict__ A, const double* __restrict__ X,
-                                              double* __restrict__ Y, int P2, double root_size,
-                                              const int* __restrict__ leaf_box, const int* __restrict__ box_level,
-                                              long sx, long sy, int ldx, int kx) {
-  static_assert(TE == 64 || MTB % 4 == 0, "TE = 16 splits the row tiles over the four waves");
-  X += blockIdx.y * sx;  // right-hand side blockIdx.y
-  Y += blockIdx.y * sy;
-  constexpr int KB = 16;
-  constexpr int LDA = TE;        // entries per LDS row (tile of TE = 64 or 16 entries)
-  constexpr int LDB = 16 * MTB;  // table rows per LDS row
-  constexpr int NACC = (TE == 64) ? MTB : MTB / 4;  // row tiles per wave
-  constexpr int BE = MTB;        // table values staged per thread and K block
-  __shared__ double sA[2][KB * LDA];
-  __shared__ double sB[2][KB * LDB];
-  const int nrb = MT / MTB;
-  // XCD-aware, persistent order: work-groups are dispatched round-robin over
-  // the 8 XCDs, so the work-groups of XCD x (blockIdx % 8 == x) walk one
-  // contiguous range of work items; consecutive items share a configuration
-  // and hence a table, which that XCD's L2 then serves to all of them.
-  const int nb = gridDim.x, bb = blockIdx.x;
-  const int x = bb & 7;
-  const int q = nitems >> 3, rr = nitems & 7;
-  const int xfirst = x * q + min(x, rr), xcount = q + (x < rr ? 1 : 0);
-  const int xwgs = (nb - x + 7) >> 3;  // work-groups on this XCD
-  for (int j = bb >> 3; j < xcount; j += xwgs) {
-  const int item = xfirst + j;
-  const int tile = item / nrb, rb = item - tile * nrb;
-  const int c = t_cfg[tile], p0 = t_first[tile], np = t_count[tile];
-  const int R = 16 * MT;
-  const int row0 = 16 * MTB * rb;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const double* Ac = A + (size_t)c * KD * R;
-  // global -> register staging of one K block
-  constexpr int AE = TE * KB / 256;                  // entry values per thread (4 or 1)
-  const int aj = tid % TE, ak = (tid / TE) * AE;     // entry aj, k = ak..ak+AE-1
-  // table block KB x LDB: thread tid stages the values tid, tid + 256, ...
-  // (v = k * LDB + row), so consecutive lanes touch consecutive rows
-  const bool a_ok = aj < np;
-  const double* xsrc = X + (size_t)(a_ok ? src[p0 + aj] : 0) * ldx;
-  double ra[AE], rbv[BE];
-  auto gload = [&](int kb) {
-    const int k0 = kb * KB;
-#pragma unroll
-    for (int e = 0; e < AE; ++e) ra[e] = (a_ok && k0 + ak + e < kx) ? xsrc[k0 + ak + e] : 0.0;
-#pragma unroll
-    for (int e = 0; e < BE; ++e) {
-      const int v = tid + 256 * e, bk = v / LDB, br = v - bk * LDB;
-      rbv[e] = Ac[(size_t)(k0 + bk) * R + row0 + br];
-    }
-  };
-  auto lstore = [&](int buf) {
-#pragma unroll
-    for (int e = 0; e < AE; ++e) sA[buf][(ak + e) * LDA + aj] = ra[e];
-#pragma unroll
-    for (int e = 0; e < BE; ++e) sB[buf][tid + 256 * e] = rbv[e];
-  };
-  // wave w: TE = 64 -> entries 16w..16w+15, every row tile;
-  //         TE = 16 -> entries 0..15, row tiles w, w+4
-  const int ebase = (TE == 64) ? 16 * w : 0;
-  auto tile_of = [&](int r) { return (TE == 64) ? r : w + 4 * r; };
-  vfx_d4 acc[NACC];
-#pragma unroll
-  for (int r = 0; r < NACC; ++r) acc[r] = vfx_d4{0, 0, 0, 0};
-  constexpr int NKB = KD / KB;
-  __syncthreads();  // the previous item is done with the LDS buffers
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int kb = 0; kb < NKB; ++kb) {
-    const int buf = kb & 1;
-    if (kb + 1 < NKB) gload(kb + 1);
-#pragma unroll
-    for (int ks = 0; ks < KB / 4; ++ks) {
-      const int k = 4 * ks + lk;
-      const double a = sA[buf][k * LDA + ebase + li];
-      double bv[NACC];
-#pragma unroll
-      for (int r = 0; r < NACC; ++r) bv[r] = sB[buf][k * LDB + 16 * tile_of(r) + li];
-#pragma unroll
-      for (int r = 0; r < NACC; ++r) acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[r], acc[r], 0, 0, 0);
-    }
-    if (kb + 1 < NKB) lstore(buf ^ 1);
-    __syncthreads();
-  }
-#pragma unroll
-  for (int r = 0; r < NACC; ++r) {
-    const int row = row0 + 16 * tile_of(r) + li;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int ent = ebase + lk + 4 * e;
-      if (ent >= np) continue;
-      if (EPI == 0) {
-        Y[(size_t)(p0 + ent) * R + row] = acc[r][e];
-      } else if (row < P2) {
-        const int leaf = src[p0 + ent];
-        const int b = leaf_box[leaf];
-        const double h = box_side(root_size, box_level[b]);
-        Y[(size_t)b * P2 + row] = h * h * acc[r][e];
-      }
-    }
-  }
-  }  // work items
-}
-
-// -------------------------------------------------------------------------
-// Table GEMMs with 64-entry tiles and K a multiple of 32 (near field dense
-// operators, P2L, M2P, P2M for K = 8 and 16): the same products as k_gemm with a
-// deeper pipeline.  A work item is a tile of <= 64 entries of one
-// configuration and a block of MTB row tiles; wave w owns the entries
-// 16w..16w+15.  The entry operands go straight from memory into a ring of
+// A work item is a tile of <= 64 entries of one configuration and a block of
+// MTB row tiles; wave w owns the entries 16w..16w+15.  The entry operands go straight from memory into a ring of
 // three register blocks (contraction order permuted so that a lane reads 64
 // contiguous bytes per block: MFMA step s of block kb pairs k = 32kb +
 // 8(l/16) + s with lane l on both sides); the table block (32 k x 16 MTB
@@ -699,8 +571,11 @@ __global__ void __launch_bounds__(256) k_gemm(int nitems, int MT, const int* __r
 // blocks into double-buffered LDS.  Every global load is issued two
 // compute phases before its data is needed.  LDS rows are 16 MTB + 2
 // doubles apart, so the two lane groups of a half-wave (rows 8 apart) fall
-// into opposite halves of the banks.  Persistent, XCD-aware item order as in
-// k_gemm.
+// into opposite halves of the banks.  XCD-aware, persistent order:
+// work-groups are dispatched round-robin over the 8 XCDs, so those of XCD x
+// (blockIdx % 8 == x) walk one contiguous range of work items; consecutive
+// items share a configuration and hence a table, which that XCD's L2 then
+// serves to all of them.
 // calls f(integral_constant<int, I>) for I = I0 .. N-1 (ring indices in an
 // unrolled pipeline stay compile-time constants)
 template <int I, int N, class F>
@@ -711,13 +586,12 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int KD, int MTB, int EPI>
+template <int KD, int MTB>
 __global__ void __launch_bounds__(256) k_tgemm(int nitems, int MT, const int* __restrict__ t_cfg,
                                                const int* __restrict__ t_first, const int* __restrict__ t_count,
                                                const int* __restrict__ src, const double* __restrict__ A,
                                                const double* __restrict__ X, double* __restrict__ Y, long sx,
-                                               long sy, int ldx, int kx, int P2, double root_size,
-                                               const int* __restrict__ leaf_box, const int* __restrict__ box_level) {
+                                               long sy, int ldx, int kx) {
   static_assert(KD % 32 == 0, "contraction in blocks of 32");
   X += blockIdx.y * sx;  // right-hand side blockIdx.y
   Y += blockIdx.y * sy;
@@ -803,213 +677,14 @@ __global__ void __launch_bounds__(256) k_tgemm(int nitems, int MT, const int* __
       __syncthreads();
     });
     // outputs D[lk + 4e][16 r + li]: entry 16w + lk + 4e, row row0 + 16r + li
-    // (EPI = 1: rows < 2P of a leaf, scaled by h^2, into its multipole)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int en = 16 * w + lk + 4 * e;
       if (en >= np) continue;
-      if constexpr (EPI == 0) {
 #pragma unroll
-        for (int r = 0; r < MTB; ++r) Y[(size_t)(p0 + en) * R + row0 + 16 * r + li] = acc[r][e];
-      } else {
-        const int b = leaf_box[src[p0 + en]];
-        const double h = box_side(root_size, box_level[b]);
-#pragma unroll
-        for (int r = 0; r < MTB; ++r) {
-          const int row = row0 + 16 * r + li;
-          if (row < P2) Y[(size_t)b * P2 + row] = h * h * acc[r][e];
-        }
-      }
+      for (int r = 0; r < MTB; ++r) Y[(size_t)(p0 + en) * R + row0 + 16 * r + li] = acc[r][e];
     }
   }
-}
-
-// -------------------------------------------------------------------------
-// Near field in low-rank form, for the configurations c whose operator
-// factorises as Q_c W_c (rank R_c <= 64, padded to a multiple of 16).  A
-// work item is a tile of <= 32 list-1 pairs of one configuration:
-//   Z = X W_c^T  (pairs x R_c: the source leaf values times the row factor),
-//   Y = Z Q_c^T  (pairs x n),
-// both as FP64 MFMA tile products.  Wave w = pg + 2 hf works on the pair
-// group pg (pairs 16pg..16pg+15): in phase 1 on the source nodes of half hf
-// (the two partial Z of a pair group meet in LDS), in phase 2 on the target
-// rows of half hf.  So a wave carries half of a 16-pair share of the work,
-// and a few hundred tiles spread evenly over the SIMDs.  Phase 1 takes its A
-// operands (the wave's own source rows) straight from memory into a ring of
-// three register blocks, with the contraction order permuted so that a lane
-// reads 16 contiguous bytes per block of 8 nodes; W_c, shared by the four
-// waves, goes through a ring of two register blocks into double-buffered
-// LDS (both halves' rows of a block at once), and Q_c the same way, 4 ranks
-// per block.  Every global load is issued two compute phases before its
-// data is needed.  With about 51 KB of LDS and <= 168 VGPRs three
-// work-groups share a CU.  Persistent, XCD-aware item order as in k_gemm
-// (items are configuration-major, so an XCD's L2 holds the factors of the
-// few configurations it works on).
-// LDS row strides: W rows 72 doubles (the lane groups of a half-wave read
-// rows 2 apart: 2 x 72 x 8 bytes = 128 mod 256, opposite halves of the
-// banks); Q rows 272 doubles (rows 1 apart: 272 x 8 = 128 mod 256).
-constexpr int kLrKB = 8, kLrLDW = 72, kLrLDZ = kNearLrMax + 1, kLrQB = 4, kLrLDQ = 272;
-constexpr int kLrTile = 32;
-
-template <int KD, int MT1>
-__device__ __forceinline__ void near_lr_item(const double* __restrict__ xrow, const double* __restrict__ Wc,
-                                             const double* __restrict__ Qc, double* sbuf, double* sZ,
-                                             double* __restrict__ Yp, int np) {
-  constexpr int LM = kNearLrMax, HK = KD / 2, NKB = HK / kLrKB, R = 16 * MT1;
-  constexpr int NQB = R / kLrQB, NRT2 = HK / 16;
-  static_assert(2 * 2 * kLrKB * kLrLDW >= 2 * kLrQB * kLrLDQ && KD <= kLrLDQ, "staging buffer sizes");
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int pg = w & 1, hf = w >> 1;
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  // ---- phase 1: partial Z over the source nodes of half hf; MFMA step s of
-  // block kb pairs node HK hf + 8kb + 2(l/16) + s with lane l on both sides
-  vfx_d2 ra[3], rw[2][2];
-  auto ga = [&](auto kbc, auto slc) __attribute__((always_inline)) {
-    constexpr int kb = decltype(kbc)::value, sl = decltype(slc)::value;
-    ra[sl] = *(const vfx_d2*)(xrow + kLrKB * kb);
-  };
-  // W block: rows 8kb..8kb+7 of both halves (LDS rows 0..7 half 0, 8..15
-  // half 1), 16-byte pieces q = tid + 256 e
-  auto gw = [&](auto kbc, auto slc) __attribute__((always_inline)) {
-    constexpr int kb = decltype(kbc)::value, sl = decltype(slc)::value;
-    static_for<0, 2>([&](auto ec) __attribute__((always_inline)) {
-      constexpr int e = decltype(ec)::value;
-      const int q = tid + 256 * e, r16 = q >> 5, col = 2 * (q & 31);
-      const int row = (r16 >> 3) * HK + kLrKB * kb + (r16 & 7);
-      rw[sl][e] = col < R ? *(const vfx_d2*)(Wc + (size_t)row * LM + col) : vfx_d2{0.0, 0.0};
-    });
-  };
-  auto sw = [&](auto bufc, auto slc) __attribute__((always_inline)) {
-    constexpr int bf = decltype(bufc)::value, sl = decltype(slc)::value;
-    static_for<0, 2>([&](auto ec) __attribute__((always_inline)) {
-      constexpr int e = decltype(ec)::value;
-      const int q = tid + 256 * e, r16 = q >> 5, col = 2 * (q & 31);
-      *(vfx_d2*)(sbuf + (bf * 2 * kLrKB + r16) * kLrLDW + col) = rw[sl][e];
-    });
-  };
-  vfx_d4 acc[MT1];
-#pragma unroll
-  for (int r = 0; r < MT1; ++r) acc[r] = vfx_d4{0, 0, 0, 0};
-  ga(I0{}, I0{});
-  gw(I0{}, I0{});
-  ga(I1{}, I1{});
-  gw(I1{}, I1{});
-  __syncthreads();  // the previous item is done with sbuf and sZ
-  sw(I0{}, I0{});
-  __syncthreads();
-  static_for<0, NKB>([&](auto kbc) __attribute__((always_inline)) {
-    constexpr int kb = decltype(kbc)::value;
-    if constexpr (kb + 2 < NKB) {
-      ga(std::integral_constant<int, kb + 2>{}, std::integral_constant<int, (kb + 2) % 3>{});
-      gw(std::integral_constant<int, kb + 2>{}, std::integral_constant<int, kb % 2>{});
-    }
-    const double* sb = sbuf + ((kb % 2) * 2 * kLrKB + kLrKB * hf + 2 * lk) * kLrLDW + li;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const double av = ra[kb % 3][s];
-      double bv[MT1];
-#pragma unroll
-      for (int r = 0; r < MT1; ++r) bv[r] = sb[s * kLrLDW + 16 * r];
-#pragma unroll
-      for (int r = 0; r < MT1; ++r) acc[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[r], acc[r], 0, 0, 0);
-    }
-    if constexpr (kb + 1 < NKB)
-      sw(std::integral_constant<int, (kb + 1) % 2>{}, std::integral_constant<int, (kb + 1) % 2>{});
-    __syncthreads();
-  });
-  // partial Z of half hf for the pair group's rows: D[lk + 4e][16 r + li]
-  double* sZh = sZ + hf * kLrTile * kLrLDZ;
-#pragma unroll
-  for (int r = 0; r < MT1; ++r)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) sZh[(16 * pg + lk + 4 * e) * kLrLDZ + 16 * r + li] = acc[r][e];
-  // ---- phase 2: rows HK hf.. of Y = Z Q^T, Z = the sum of the two partials;
-  // Q block = 4 ranks x n rows, pieces v = tid + 256 e
-  vfx_d2 rq[2][2];
-  auto gq = [&](auto qbc, auto slc) __attribute__((always_inline)) {
-    constexpr int qb = decltype(qbc)::value, sl = decltype(slc)::value;
-    static_for<0, 2>([&](auto ec) __attribute__((always_inline)) {
-      constexpr int e = decltype(ec)::value;
-      const int v = tid + 256 * e, rank = v / (KD / 2), col = 2 * (v % (KD / 2));
-      rq[sl][e] = *(const vfx_d2*)(Qc + (size_t)(kLrQB * qb + rank) * KD + col);
-    });
-  };
-  auto sq = [&](auto bufc, auto slc) __attribute__((always_inline)) {
-    constexpr int bf = decltype(bufc)::value, sl = decltype(slc)::value;
-    static_for<0, 2>([&](auto ec) __attribute__((always_inline)) {
-      constexpr int e = decltype(ec)::value;
-      const int v = tid + 256 * e, rank = v / (KD / 2), col = 2 * (v % (KD / 2));
-      *(vfx_d2*)(sbuf + (bf * kLrQB + rank) * kLrLDQ + col) = rq[sl][e];
-    });
-  };
-  vfx_d4 acc2[NRT2];
-#pragma unroll
-  for (int r = 0; r < NRT2; ++r) acc2[r] = vfx_d4{0, 0, 0, 0};
-  gq(I0{}, I0{});
-  if constexpr (NQB > 1) gq(I1{}, I1{});
-  __syncthreads();  // phase 1 is done with sbuf; both partial Z complete
-  sq(I0{}, I0{});
-  __syncthreads();
-  const double* z0 = sZ + (16 * pg + li) * kLrLDZ + lk;
-  const double* z1 = z0 + kLrTile * kLrLDZ;
-  static_for<0, NQB>([&](auto qbc) __attribute__((always_inline)) {
-    constexpr int qb = decltype(qbc)::value;
-    if constexpr (qb + 2 < NQB) gq(std::integral_constant<int, qb + 2>{}, std::integral_constant<int, qb % 2>{});
-    const double a = z0[kLrQB * qb] + z1[kLrQB * qb];
-    const double* qrow = sbuf + ((qb % 2) * kLrQB + lk) * kLrLDQ + HK * hf + li;
-#pragma unroll
-    for (int r = 0; r < NRT2; ++r) acc2[r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, qrow[16 * r], acc2[r], 0, 0, 0);
-    if constexpr (qb + 1 < NQB)
-      sq(std::integral_constant<int, (qb + 1) % 2>{}, std::integral_constant<int, (qb + 1) % 2>{});
-    __syncthreads();
-  });
-#pragma unroll
-  for (int r = 0; r < NRT2; ++r)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int ent = 16 * pg + lk + 4 * e;
-      if (ent < np) Yp[(size_t)ent * KD + HK * hf + 16 * r + li] = acc2[r][e];
-    }
-}
-
-template <int KD>
-__global__ void __launch_bounds__(256, 3) k_near_lr(int nitems, const int* __restrict__ t_cfg,
-                                                    const int* __restrict__ t_first, const int* __restrict__ t_count,
-                                                    const int* __restrict__ src, const int* __restrict__ lr_R,
-                                                    const double* __restrict__ W, const double* __restrict__ Q,
-                                                    const double* __restrict__ X, double* __restrict__ Y, long sx,
-                                                    long sy) {
-  X += blockIdx.y * sx;  // right-hand side blockIdx.y
-  Y += blockIdx.y * sy;
-  constexpr int LM = kNearLrMax;  // 64
-  __shared__ __attribute__((aligned(16))) double sbuf[2 * 2 * kLrKB * kLrLDW];
-  __shared__ double sZ[2 * kLrTile * kLrLDZ];
-  const int nb = gridDim.x, bb = blockIdx.x;
-  const int x = bb & 7;
-  const int q = nitems >> 3, rr = nitems & 7;
-  const int xfirst = x * q + min(x, rr), xcount = q + (x < rr ? 1 : 0);
-  const int xwgs = (nb - x + 7) >> 3;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  for (int j = bb >> 3; j < xcount; j += xwgs) {
-    const int tile = xfirst + j;
-    const int c = t_cfg[tile], p0 = t_first[tile], np = t_count[tile];
-    const double* Wc = W + (size_t)c * KD * LM;
-    const double* Qc = Q + (size_t)c * LM * KD;
-    // this lane's A-operand pair (a pair past the tile's end reads the first
-    // pair's row; its results are not stored) and its half of the nodes
-    const int ent = 16 * (w & 1) + li;
-    const double* xrow = X + (size_t)src[p0 + (ent < np ? ent : 0)] * KD + (KD / 2) * (w >> 1) + 2 * lk;
-    double* Yp = Y + (size_t)p0 * KD;
-    switch (lr_R[c] >> 4) {
-      case 1: near_lr_item<KD, 1>(xrow, Wc, Qc, sbuf, sZ, Yp, np); break;
-      case 2: near_lr_item<KD, 2>(xrow, Wc, Qc, sbuf, sZ, Yp, np); break;
-      case 3: near_lr_item<KD, 3>(xrow, Wc, Qc, sbuf, sZ, Yp, np); break;
-      default: near_lr_item<KD, 4>(xrow, Wc, Qc, sbuf, sZ, Yp, np); break;
-    }
-  }  // work items
 }
 
 // -------------------------------------------------------------------------
@@ -1255,8 +930,9 @@ __global__ void __launch_bounds__(64) k_down(int Prt, double root_size, const in
 // -------------------------------------------------------------------------
 // Far field and the near-field reduction, one wave per leaf; lane l holds
 // the nodes l + 64j, j < NPL (NPL = ceil(K^2/64)): L2P of the leaf's full
-// local expansion by Horner in the scaled node position, the list-1 sums of
-// the near-field products and the list-3 sums of the M2P products (in list
+// local expansion by Horner in the scaled node position, the near field (the
+// folded row of the same-level sources, unfolded here, and the rows of the
+// other list-1 pairs) and the list-3 sums of the M2P products (in list
 // order, deterministic), and the log terms: log(h) a_0 of each list-1 source
 // and log(h/2) a_0 of each list-3 box.  Every per-leaf quantity (the local
 // expansion, the list slots) comes in with one vector load, lane k holding
@@ -1281,12 +957,14 @@ __global__ void __launch_bounds__(64) k_far(int K, int Prt, double root_size, co
                                             const int* __restrict__ l3_slot, const double* __restrict__ Y3,
                                             const double2* __restrict__ locf, const double2* __restrict__ mpole,
                                             const int* __restrict__ l1_ptr, const int* __restrict__ l1_srcbox,
-                                            const int* __restrict__ l1_slot, const double* __restrict__ Y,
-                                            double* __restrict__ V, long slf,
-                                            long smp, long sny, long sy3, long sv) {
+                                            const int* __restrict__ sy_row, const double* __restrict__ YS,
+                                            const int* __restrict__ y_ptr, const int* __restrict__ y_slot,
+                                            const double* __restrict__ Y, double* __restrict__ V, long slf, long smp,
+                                            long sys, long sny, long sy3, long sv) {
   const int P = EXACT ? PM : Prt;  // <= 64
   locf += blockIdx.y * slf;        // right-hand side blockIdx.y
   mpole += blockIdx.y * smp;
+  YS += blockIdx.y * sys;
   Y += blockIdx.y * sny;
   Y3 += blockIdx.y * sy3;
   V += blockIdx.y * sv;
@@ -1300,7 +978,9 @@ __global__ void __launch_bounds__(64) k_far(int K, int Prt, double root_size, co
   // fewer than 64), list-3 entry `lane` (at most 20), local coefficient `lane`
   const int e0 = l1_ptr[leaf], n1 = l1_ptr[leaf + 1] - e0;
   const int f0 = l3_ptr[leaf], n3 = l3_ptr[leaf + 1] - f0;
-  const int my_slot = (!NTS && lane < n1) ? l1_slot[e0 + lane] : 0;
+  const int g0 = NTS ? 0 : y_ptr[leaf], ny = NTS ? 0 : y_ptr[leaf + 1] - g0;
+  const int my_slot = (!NTS && lane < ny) ? y_slot[g0 + lane] : 0;
+  const int srow = NTS ? -1 : sy_row[leaf];
   const double my_a0 = lane < n1 ? mpole[(size_t)l1_srcbox[e0 + lane] * P].x : 0.0;
   const int my_slot3 = lane < n3 ? l3_slot[f0 + lane] : 0;
   const double my_b0 = lane < n3 ? mpole[(size_t)l3_src[f0 + lane] * P].x : 0.0;
@@ -1327,8 +1007,40 @@ __global__ void __launch_bounds__(64) k_far(int K, int Prt, double root_size, co
       for (int j = 0; j < NPL; ++j) yn[j] = V[(size_t)leaf * n + node[j]];
       for (int e = 0; e < n1; ++e) lg += readlane_d(my_a0, e);
     } else {
+      if (srow >= 0) {
+        // same-level sources: the folded row, four parities of (K/2)^2
+        const int H = K / 2;
+        const double* ys = YS + (size_t)srow * n;
+        if constexpr (NPL == 4) {
+          const int a = lane >> 2, bb = 4 * (lane & 3);
+          const bool up = bb >= 8;
+          const double sx = a < 8 ? 1.0 : -1.0, sy = up ? -1.0 : 1.0;
+          const double* r = ys + 8 * (a < 8 ? a : 15 - a) + (up ? 12 - bb : bb);
+          double w[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const double sg = ((q & 2) ? sx : 1.0) * ((q & 1) ? sy : 1.0);
+            const vfx_d2 u0 = *(const vfx_d2*)(r + 64 * q), u1 = *(const vfx_d2*)(r + 64 * q + 2);
+            w[0] += sg * u0.x;
+            w[1] += sg * u0.y;
+            w[2] += sg * u1.x;
+            w[3] += sg * u1.y;
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) yn[j] = up ? w[3 - j] : w[j];
+        } else {
+#pragma unroll
+          for (int j = 0; j < NPL; ++j) {
+            const int a = node[j] / K, b = node[j] % K;
+            const double sx = a < H ? 1.0 : -1.0, sy = b < H ? 1.0 : -1.0;
+            const double* r = ys + (a < H ? a : K - 1 - a) * H + (b < H ? b : K - 1 - b);
+            yn[j] = (r[0] + sy * r[H * H]) + sx * (r[2 * H * H] + sy * r[3 * H * H]);
+          }
+        }
+      }
+      for (int e = 0; e < n1; ++e) lg += readlane_d(my_a0, e);
 #pragma unroll 4
-      for (int e = 0; e < n1; ++e) {
+      for (int e = 0; e < ny; ++e) {
         const double* y = Y + (size_t)__builtin_amdgcn_readlane(my_slot, e) * n;
         if constexpr (NPL == 4) {
           const vfx_d2 u0 = __builtin_nontemporal_load((const vfx_d2*)(y + 4 * lane)),
@@ -1341,7 +1053,6 @@ __global__ void __launch_bounds__(64) k_far(int K, int Prt, double root_size, co
 #pragma unroll
           for (int j = 0; j < NPL; ++j) yn[j] += y[node[j]];
         }
-        lg += readlane_d(my_a0, e);
       }
     }
 #pragma unroll 4
@@ -1667,10 +1378,10 @@ int upload_tables(Context* c, std::string& err) {
   UP(D.AbarT, T.AbarT);
   UP(D.A, T.A);
   UP(D.cbar, T.cbar);
-  UP(D.near, T.near);
+  UP(D.mom_T, T.mom_T);
+  UP(D.sym_T, T.sym_T);
+  UP(D.pair_T, T.pair_T);
   UP(D.lr_R, T.lr_R);
-  UP(D.lr_W, T.lr_W);
-  UP(D.lr_Q, T.lr_Q);
   UP(D.fx_W, T.fx_W);
   UP(D.fx_Wexp, T.fx_Wexp);
   if (T.ts_ok) {
@@ -1691,7 +1402,6 @@ int upload_tables(Context* c, std::string& err) {
   UP(D.f8_Aexp, T.f8_Aexp);
   UP(D.p2l_gemm, T.p2l_gemm);
   UP(D.m2p_gemm, T.m2p_gemm);
-  UP(D.p2m_gemm, T.p2m_gemm);
   UP(D.pas_m2l, T.pas_m2l);
   UP(D.pas_m2l_t, T.pas_m2l_t);
   UP(D.pas_m2m_t, T.pas_m2m_t);
@@ -1732,11 +1442,11 @@ int upload_tables(Context* c, std::string& err) {
 void free_tables_device(Context* c) {
   DeviceTables& D = c->D;
   c->gen++;
-  void* ptrs[] = {D.t,        D.tbar,     D.w2,       D.AbarT,   D.cbar,     D.near,    D.near_s2,   D.A,
+  void* ptrs[] = {D.t,        D.tbar,     D.w2,       D.AbarT,   D.cbar,     D.mom_T,   D.sym_T,     D.pair_T,   D.A,
                   D.p2m,      D.l2p,      D.m2m,      D.l2l,     D.m2l,      D.p2l,     D.p2l_area,
-                  D.pas_m2l,  D.pas_m2m,  D.pas_l2l,  D.m2l_logd, D.p2l_gemm, D.m2p_gemm, D.m2l_tpow, D.m2l_tneg, D.p2m_gemm,
+                  D.pas_m2l,  D.pas_m2m,  D.pas_l2l,  D.m2l_logd, D.p2l_gemm, D.m2p_gemm, D.m2l_tpow, D.m2l_tneg,
                   D.m2m_in,   D.m2m_out,  D.l2l_in,   D.l2l_out,  D.pas_m2l_t, D.pas_m2m_t, D.pas_l2l_t,
-                  D.lr_R,     D.lr_W,     D.lr_Q,     D.fx_W,     D.fx_Q,     D.fx_A,     D.fx_Wexp,
+                  D.lr_R,     D.fx_W,     D.fx_Q,     D.fx_A,     D.fx_Wexp,
                   D.fx_Qexp,  D.fx_Aexp,  D.f8_W,     D.f8_Q,     D.f8_A,     D.f8_Wexp,  D.f8_Qexp,  D.f8_Aexp,
                   D.cls_R,    D.lr_Wp,    D.cls_QT,   D.self_T};
   for (void* p : ptrs)
@@ -1755,11 +1465,12 @@ int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err) {
   if (D.cap > 0) (void)hipDeviceSynchronize();  // no execute of this plan in flight
   p->gen++;  // graphs that captured the old buffers are stale
   void* old[] = {D.mpole, D.local, D.near_y, D.p2l_y, D.up_part, D.locf, D.xs, D.m2p_y, D.xs_exp, D.near_z,
-                 D.ext_fg, D.ext_g};
+                 D.ext_fg, D.ext_g, D.mom, D.ysym};
   for (void* q : old)
     if (q) (void)hipFree(q);
   D.mpole = D.local = D.up_part = D.locf = nullptr;
   D.near_y = D.p2l_y = D.m2p_y = D.near_z = nullptr;
+  D.mom = D.ysym = nullptr;
   D.xs = nullptr;
   D.xs_exp = nullptr;
   D.ext_fg = D.ext_g = nullptr;
@@ -1767,6 +1478,13 @@ int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err) {
   VFX_HIP(hipMalloc((void**)&D.mpole, sizeof(double2) * (size_t)H.B * P * R));
   VFX_HIP(hipMalloc((void**)&D.local, sizeof(double2) * (size_t)H.B * P * R));
   VFX_HIP(hipMemset(D.local, 0, sizeof(double2) * (size_t)H.B * P * R));
+  {
+    // moments; the row past the leaves is the zero source
+    const size_t wm = sizeof(double) * 4 * moment_stride(T.mom_E), rows = (size_t)H.L + 1;
+    VFX_HIP(hipMalloc((void**)&D.mom, wm * rows * R));
+    VFX_HIP(hipMemset2D((char*)D.mom + wm * H.L, wm * rows, 0, wm, R));
+  }
+  if (!H.sy_tgt.empty()) VFX_HIP(hipMalloc((void**)&D.ysym, sizeof(double) * H.sy_tgt.size() * T.n * R));
   if (!H.np_src.empty() && !H.ts) VFX_HIP(hipMalloc((void**)&D.near_y, sizeof(double) * H.np_src.size() * T.n * R));
   if (!H.np_src.empty() && H.ts)
     VFX_HIP(hipMalloc((void**)&D.near_z, sizeof(double) * H.np_src.size() * kNearLrMax * R));
@@ -1782,6 +1500,9 @@ int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err) {
     VFX_HIP(hipMalloc((void**)&D.ext_fg, sizeof(double) * (size_t)H.ncut * R * T.nG));
     VFX_HIP(hipMalloc((void**)&D.ext_g, sizeof(double) * (size_t)H.ncut * R * T.Kbar * T.Kbar));
   }
+  // the fills above run on the null stream, which the executes' streams need
+  // not wait for
+  VFX_HIP(hipStreamSynchronize(nullptr));
   D.cap = nrhs;
   return VFX_OK;
 }
@@ -1831,10 +1552,10 @@ int upload_plan(Plan* p, std::string& err) {
   UP(D.l4_src, H.l4_src);
   UP(D.l4_cfg, H.l4_cfg);
   UP(D.np_src, H.np_src);
-  UP(D.l1_slot, H.l1_slot);
-  UP(D.nt_cfg, H.nt_cfg);
-  UP(D.nt_first, H.nt_first);
-  UP(D.nt_count, H.nt_count);
+  UP(D.y_ptr, H.y_ptr);
+  UP(D.y_slot, H.y_slot);
+  UP(D.sy_nb, H.sy_nb);
+  UP(D.sy_row, H.sy_row);
   UP(D.nl_cfg, H.nl_cfg);
   UP(D.nl_first, H.nl_first);
   UP(D.nl_count, H.nl_count);
@@ -1859,9 +1580,6 @@ int upload_plan(Plan* p, std::string& err) {
   UP(D.t3_cfg, H.t3_cfg);
   UP(D.t3_first, H.t3_first);
   UP(D.t3_count, H.t3_count);
-  UP(D.t0_cfg, H.t0_cfg);
-  UP(D.t0_first, H.t0_first);
-  UP(D.t0_count, H.t0_count);
   UP(D.leaf_ids, H.leaf_ids);
 
   UP(D.cut_leaf, H.cut_leaf);
@@ -1887,6 +1605,7 @@ int upload_plan(Plan* p, std::string& err) {
   VFX_HIP(hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming));
   VFX_HIP(hipEventCreateWithFlags(&p->p2l_ev, hipEventDisableTiming));
   VFX_HIP(hipEventCreateWithFlags(&p->up_ev, hipEventDisableTiming));
+  VFX_HIP(hipEventCreateWithFlags(&p->mom_ev, hipEventDisableTiming));
   D.ready = true;
   return VFX_OK;
 }
@@ -1897,11 +1616,11 @@ void free_plan_device(Plan* p) {
   p->gen++;
   void* ptrs[] = {D.box_level, D.box_child0, D.box_leaf, D.box_parent, D.box_cx,   D.box_cy,   D.leaf_box,
                   D.kind,      D.l1_ptr,     D.l1_src,   D.l1_cfg,     D.l2_ptr,   D.l2_src,   D.l2_off,
-                  D.l3_ptr,    D.l3_src,     D.l4_ptr,   D.l4_src,     D.l4_cfg,   D.np_src,   D.l1_slot,
-                  D.nt_cfg,    D.nt_first,   D.nt_count, D.near_y,     D.p4_src,   D.l4_slot,  D.t4_cfg,
+                  D.l3_ptr,    D.l3_src,     D.l4_ptr,   D.l4_src,     D.l4_cfg,   D.np_src,   D.y_ptr,
+                  D.y_slot,    D.sy_nb,      D.sy_row,   D.near_y,     D.p4_src,   D.l4_slot,  D.t4_cfg,
                   D.t4_first,  D.t4_count,   D.p2l_y,    D.cut_leaf,   D.ext_ptr,  D.ext_tgt,  D.pinv_ptr,
-                  D.pinv_idx,  D.pinv_val,   D.sbar_given, D.mpole,    D.local,    D.t0_cfg,   D.t0_first,
-                  D.t0_count,  D.leaf_ids,   D.l2_tgt,   D.m2l_grp,  D.up_box,   D.up_ptr,   D.up_src,
+                  D.pinv_idx,  D.pinv_val,   D.sbar_given, D.mpole,    D.local,    D.mom,
+                  D.ysym,      D.leaf_ids,   D.l2_tgt,   D.m2l_grp,  D.up_box,   D.up_ptr,   D.up_src,
                   D.up_pos,    D.up_split,   D.up_grp,   D.up_part,  D.anc_ptr,  D.anc,
                   D.nl_cfg,    D.nl_first,   D.nl_count, D.l1_srcbox,  D.ext_geo,
                   D.anc_leaf,  D.dn_grp,     D.locf,     D.mt_cfg,   D.mt_first, D.mt_count, D.ml_cfg, D.fac_ws,
@@ -1920,8 +1639,9 @@ void free_plan_device(Plan* p) {
   if (p->join_ev) (void)hipEventDestroy(p->join_ev);
   if (p->p2l_ev) (void)hipEventDestroy(p->p2l_ev);
   if (p->up_ev) (void)hipEventDestroy(p->up_ev);
+  if (p->mom_ev) (void)hipEventDestroy(p->mom_ev);
   if (p->side) (void)hipStreamDestroy(p->side);
-  p->fork_ev = p->join_ev = p->p2l_ev = p->up_ev = nullptr;
+  p->fork_ev = p->join_ev = p->p2l_ev = p->up_ev = p->mom_ev = nullptr;
   p->side = nullptr;
 }
 
@@ -1934,74 +1654,14 @@ static int persistent_grid(int items, int max_wgs) {
   return std::max(grid, std::min(items, 8));
 }
 
-template <int KD, int EPI, int TE, int MTB>
+template <int KD, int MTB>
 static void launch_gemm(int ntiles, int MT, const int* cfg, const int* first, const int* count, const int* src,
-                        const double* A, const double* X, double* Y, int P2, double root, const int* leaf_box,
-                        const int* box_level, hipStream_t s, int max_wgs, unsigned R, long sx, long sy,
-                        int ldx = KD, int kx = KD) {
+                        const double* A, const double* X, double* Y, hipStream_t s, int max_wgs, unsigned R, long sx,
+                        long sy, int ldx = KD, int kx = KD) {
   const int items = ntiles * (MT / MTB);
   const int grid = persistent_grid(items, max_wgs);
-  if constexpr (TE == 64 && KD % 32 == 0)
-    hipLaunchKernelGGL((k_tgemm<KD, MTB, EPI>), dim3(grid, R), dim3(256), 0, s, items, MT, cfg, first, count, src, A,
-                       X, Y, sx, sy, ldx, kx, P2, root, leaf_box, box_level);
-  else
-    hipLaunchKernelGGL((k_gemm<KD, EPI, TE, MTB>), dim3(grid, R), dim3(256), 0, s, items, MT, cfg, first, count,
-                       src, A, X, Y, P2, root, leaf_box, box_level, sx, sy, ldx, kx);
-}
-
-// Dense near-field tables: MT = n/16 row tiles (1, 4, 9 or 16 for K = 4, 8,
-// 12, 16), in blocks of MTB = 1, 4, 9, 4.
-static void near_gemm(int n, int ntiles, const int* cfg, const int* first, const int* count, const int* src,
-                      const double* A, const double* X, double* Y, hipStream_t s, int max_wgs, int mtb, unsigned R,
-                      long sx, long sy) {
-  if (ntiles <= 0) return;
-  const int MT = n / 16;
-#define VFX_NG(KDV, MTBV) \
-  launch_gemm<KDV, 0, 64, MTBV>(ntiles, MT, cfg, first, count, src, A, X, Y, 0, 0, nullptr, nullptr, s, max_wgs, R, sx, sy)
-  switch (n) {
-    case 16: VFX_NG(16, 1); break;
-    case 64: VFX_NG(64, 4); break;
-    case 144: VFX_NG(144, 9); break;
-    default:
-      if (mtb == 8)
-        VFX_NG(256, 8);
-      else
-        VFX_NG(256, 4);
-      break;
-  }
-#undef VFX_NG
-}
-
-// P2L (EPI 0, TE 64) and P2M (EPI 1, TE 64) tables: rows padded to a
-// multiple of 64, so MT is 4 or 8; P2L takes them in one row block, P2M
-// (one tile per 64 leaves, few tiles) two row tiles per work item on the
-// pipelined kernel, for more items in flight (one row tile per item rereads
-// the leaf data four times, four per item leaves most CUs idle).
-template <int EPI, int TE>
-static void expansion_gemm(int n, int ntiles, int MT, const int* cfg, const int* first, const int* count,
-                           const int* src, const double* A, const double* X, double* Y, hipStream_t s, unsigned R,
-                           long sx, long sy, int P2 = 0, double root = 0, const int* leaf_box = nullptr,
-                           const int* box_level = nullptr) {
-  if (ntiles <= 0) return;
-#define VFX_EXP_CASE(KDV)                                                                                       \
-  do {                                                                                                          \
-    if (EPI == 1 && KDV % 32 == 0)                                                                              \
-      launch_gemm<KDV, EPI, TE, 2>(ntiles, MT, cfg, first, count, src, A, X, Y, P2, root, leaf_box, box_level, s, 0, \
-                                   R, sx, sy);                                                                  \
-    else if (MT == 4)                                                                                           \
-      launch_gemm<KDV, EPI, TE, 4>(ntiles, MT, cfg, first, count, src, A, X, Y, P2, root, leaf_box, box_level, s, 0, \
-                                   R, sx, sy);                                                                  \
-    else                                                                                                        \
-      launch_gemm<KDV, EPI, TE, 8>(ntiles, MT, cfg, first, count, src, A, X, Y, P2, root, leaf_box, box_level, s, 0, \
-                                   R, sx, sy);                                                                  \
-  } while (0)
-  switch (n) {
-    case 16: VFX_EXP_CASE(16); break;
-    case 64: VFX_EXP_CASE(64); break;
-    case 144: VFX_EXP_CASE(144); break;
-    default: VFX_EXP_CASE(256); break;
-  }
-#undef VFX_EXP_CASE
+  hipLaunchKernelGGL((k_tgemm<KD, MTB>), dim3(grid, R), dim3(256), 0, s, items, MT, cfg, first, count, src, A, X, Y,
+                     sx, sy, ldx, kx);
 }
 
 // M2P tables: contraction over the 2P real coefficients of a multipole
@@ -2013,8 +1673,7 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
   if (ntiles <= 0) return;
   const int MT = n / 16;
 #define VFX_M2P(KDV, MTBV)                                                                                        \
-  launch_gemm<KDV, 0, 64, MTBV>(ntiles, MT, cfg, first, count, src, A, X, Y, 0, 0, nullptr, nullptr, s, 0, R, sx, \
-                                sy, P2, P2)
+  launch_gemm<KDV, MTBV>(ntiles, MT, cfg, first, count, src, A, X, Y, s, 0, R, sx, sy, P2, P2)
 #define VFX_M2P_N(KDV)            \
   switch (n) {                    \
     case 16: VFX_M2P(KDV, 1); break;  \
@@ -2057,7 +1716,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   const int n = T.n, P = T.p + 1, L = H.L;
   // per-right-hand-side strides (elements) of the batched buffers
   const long sFL = (long)L * n, sFC = (long)H.ncut * T.nX, sMP = (long)H.B * P;
-  const long sNY = (long)H.np_src.size() * n, sPL = (long)H.p4_src.size() * T.p2l_rows;
+  const long sNY = (long)H.np_src.size() * n, sYS = (long)H.sy_tgt.size() * n, sPL = (long)H.p4_src.size() * T.p2l_rows;
   const long sNZ = (long)H.np_src.size() * kNearLrMax;
   const long sM3 = (long)H.p3_src.size() * n;
   const long sUP = (long)H.up_slots * P, sLF = (long)L * P;
@@ -2076,9 +1735,9 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   // events on the caller's stream: 0 start, 12 after f^e initialisation, 1
   // after the extension, 2 after P2M and the upward pass, 3 after M2L, 4
   // after the downward pass, 8 after the join, 9 end; on the side stream: 10
-  // start, 5 after P2L, 6 after the first near-field kernel (low-rank pairs,
+  // start, 5 after P2L, 6 after the first near-field kernel (the FP64 pairs,
   // or the factor products of the target-stationary path), 7 after the
-  // second (dense pairs, or the per-target-group kernel), 13 after the wait
+  // second (the pairs in mixed precision, or the per-target-group kernel), 13 after the wait
   // for the upward pass, 11 after M2P
   auto mark = [&](int k, hipStream_t st) -> int {
     if (timed) {
@@ -2120,30 +1779,42 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   }
   VFX_HIP(hipGetLastError());
   MARK(1, s);
-  // fork: P2L and the near field on the side stream, concurrent with P2M,
-  // the upward pass, M2L and the downward pass on the caller's stream.  The
-  // near-field grids are bounded (about two work-groups per CU, looping over
-  // the tiles).
-  VFX_HIP(hipEventRecord(p->fork_ev, s));
-  VFX_HIP(hipStreamWaitEvent(p->side, p->fork_ev, 0));
-  // P2L first on the side stream (it needs only f^e; M2L on the caller's
-  // stream waits for it), then the near field
+  // fork: P2L and the near field on the side stream, concurrent with the
+  // upward pass, M2L and the downward pass on the caller's stream.  The
+  // persistent near-field grids are bounded (about two work-groups per CU,
+  // looping over the tiles).  With a mixed near field the slices of f^e are
+  // cut beside the moments, else the side stream starts after them.
+  const bool mixed = H.precision >= 1 && !H.ts && !(H.ml_cfg.empty() && H.mt_cfg.empty());
+  if (mixed) {
+    VFX_HIP(hipEventRecord(p->fork_ev, s));
+    VFX_HIP(hipStreamWaitEvent(p->side, p->fork_ev, 0));
+    int rc = H.precision == 2 ? launch_split_f8(p, fe, nrhs, p->side, err) : launch_split_fx(p, fe, nrhs, p->side, err);
+    if (rc) return rc;
+  }
+  // exterior moments and multipoles of the leaves
+  {
+    int rc = launch_moments(p, fe, nrhs, s, err);
+    if (rc) return rc;
+  }
+  VFX_HIP(hipEventRecord(p->mom_ev, s));
+  VFX_HIP(hipStreamWaitEvent(p->side, p->mom_ev, 0));
+  // P2L first on the side stream (M2L on the caller's stream waits for it),
+  // then the near field
   MARK(10, p->side);
-  if (H.nlev > 2)
-    expansion_gemm<0, 64>(n, (int)H.t4_cfg.size(), T.p2l_rows / 16, D.t4_cfg, D.t4_first, D.t4_count, D.p4_src,
-                          DT.p2l_gemm, fe, D.p2l_y, p->side, R, sFL, sPL);
-  VFX_HIP(hipGetLastError());
+  if (H.nlev > 2) {
+    int rc = launch_p2l(p, nrhs, p->side, err);
+    if (rc) return rc;
+  }
   VFX_HIP(hipEventRecord(p->p2l_ev, p->side));
   MARK(5, p->side);
-  const long total = (long)L * n;
   if (H.ts) {
     // target-stationary near field: the factor products Z = (W_b P_g^T) f
     // of every non-self pair (table GEMM over the configuration-major
     // tiles), then the per-target-group kernel, which leaves h^2 times each
     // leaf's list-1 table sum in V
     if (!H.nl_cfg.empty())
-      launch_gemm<256, 0, 64, 4>((int)H.nl_cfg.size(), 4, D.nl_cfg, D.nl_first, D.nl_count, D.np_src, DT.lr_Wp, fe,
-                                 D.near_z, 0, 0, nullptr, nullptr, p->side, p->tune.near_wgs, R, sFL, sNZ);
+      launch_gemm<256, 4>((int)H.nl_cfg.size(), 4, D.nl_cfg, D.nl_first, D.nl_count, D.np_src, DT.lr_Wp, fe,
+                          D.near_z, p->side, p->tune.near_wgs, R, sFL, sNZ);
     VFX_HIP(hipGetLastError());
     MARK(6, p->side);
     {
@@ -2151,31 +1822,20 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
       if (rc) return rc;
     }
   } else {
-    if (!H.nl_cfg.empty()) {
-      const int items = (int)H.nl_cfg.size();
-      hipLaunchKernelGGL(k_near_lr<256>, dim3(persistent_grid(items, p->tune.near_wgs), R), dim3(256), 0, p->side, items,
-                         D.nl_cfg, D.nl_first, D.nl_count, D.np_src, DT.lr_R, DT.lr_W, DT.lr_Q, fe, D.near_y, sFL,
-                         sNY);
-    }
-    if (H.precision >= 1) {
-      // pairs in mixed precision: fixed-point bf16 (mode 1) or int8 (mode 2)
-      // slices of the leaf data, then their low-rank and self products (FP64
-      // results, same buffer)
-      int rc = H.precision == 2 ? launch_near_f8(p, fe, nrhs, p->tune.near_wgs, p->side, err)
-                                : launch_near_fx(p, fe, nrhs, p->tune.near_wgs, p->side, err);
+    int rc = launch_near_sym(p, fe, nrhs, p->tune.near_wgs, p->side, err);
+    if (rc) return rc;
+    MARK(6, p->side);
+    if (mixed) {
+      // pairs in mixed precision: the low-rank and self products of the
+      // fixed-point bf16 (mode 1) or int8 (mode 2) slices (FP64 results, rows
+      // of the same buffer)
+      rc = H.precision == 2 ? launch_near_f8(p, nrhs, p->tune.near_wgs, p->side, err)
+                            : launch_near_fx(p, nrhs, p->tune.near_wgs, p->side, err);
       if (rc) return rc;
     }
-    VFX_HIP(hipGetLastError());
-    MARK(6, p->side);
-    near_gemm(n, (int)H.nt_cfg.size(), D.nt_cfg, D.nt_first, D.nt_count, D.np_src, DT.near, fe, D.near_y, p->side,
-              p->tune.near_wgs, p->tune.dense_mtb, R, sFL, sNY);
   }
   VFX_HIP(hipGetLastError());
   MARK(7, p->side);
-  // multipoles of the leaves
-  expansion_gemm<1, 64>(n, (int)H.t0_first.size(), T.p2l_rows / 16, D.t0_cfg, D.t0_first, D.t0_count, D.leaf_ids,
-                        DT.p2m_gemm, fe, (double*)D.mpole, s, R, sFL, 2 * sMP, 2 * P, T.root_size, D.leaf_box,
-                        D.box_level);
   if (!H.up_grp.empty()) {
     const int ng = (int)H.up_grp.size() / 5;
 #define VFX_UP(PMV, EX)                                                                                            \
@@ -2269,7 +1929,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
 #define VFX_FAR(PMV, EX, NPLV, TSV)                                                                            \
   hipLaunchKernelGGL((k_far<PMV, EX, NPLV, TSV>), dim3(L, R), dim3(64), 0, s, T.K, P, T.root_size, D.leaf_box,      \
                      D.box_level, DT.t, D.l3_ptr, D.l3_src, D.l3_slot, D.m2p_y, D.locf, D.mpole, D.l1_ptr,         \
-                     D.l1_srcbox, D.l1_slot, D.near_y, V, sLF, sMP, sNY, sM3, sFL)
+                     D.l1_srcbox, D.sy_row, D.ysym, D.y_ptr, D.y_slot, D.near_y, V, sLF, sMP, sYS, sNY, sM3, sFL)
 #define VFX_FAR_N(PMV, EX)      \
   if (npl == 4 && H.ts)         \
     VFX_FAR(PMV, EX, 4, true);  \

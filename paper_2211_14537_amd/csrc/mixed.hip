@@ -366,12 +366,21 @@ int persistent_grid_fx(int items, int max_wgs) {
 
 }  // namespace
 
-int launch_near_fx(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err) {
+int launch_split_fx(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err) {
+  hipLaunchKernelGGL(k_split4, dim3(p->H.L, nrhs), dim3(256), 0, s, p->H.L, fe, p->D.xs, p->D.xs_exp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    err = std::string("mixed near field: ") + hipGetErrorString(e);
+    return VFX_EHIP;
+  }
+  return VFX_OK;
+}
+
+int launch_near_fx(const Plan* p, int nrhs, int max_wgs, hipStream_t s, std::string& err) {
   const HostPlan& H = p->H;
   const DevicePlan& D = p->D;
   const DeviceTables& DT = p->ctx->D;
   const long total = (long)H.L * kFxN, sNY = (long)H.np_src.size() * kFxN;
-  hipLaunchKernelGGL(k_split4, dim3(H.L, nrhs), dim3(256), 0, s, H.L, fe, D.xs, D.xs_exp);
   if (!H.ml_cfg.empty()) {
     const int items = (int)H.ml_cfg.size();
     hipLaunchKernelGGL(k_near_fx<true>, dim3(persistent_grid_fx(items, max_wgs), nrhs), dim3(256), 0, s, items, 1,

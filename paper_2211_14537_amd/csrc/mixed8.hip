@@ -352,15 +352,25 @@ int persistent_grid_f8(int items, int max_wgs) {
 
 }  // namespace
 
-int launch_near_f8(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err) {
+int launch_split_f8(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err) {
+  // kF8Slices x L x n bytes per right-hand side fit the 4 x L x n bf16 slices' buffer
+  static_assert(kF8Slices <= 8, "leaf slices exceed the slice buffer");
+  hipLaunchKernelGGL(k_split_i8, dim3((p->H.L + 3) / 4, nrhs), dim3(256), 0, s, p->H.L, fe, (int8_t*)p->D.xs,
+                     p->D.xs_exp);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    err = std::string("mixed near field (int8): ") + hipGetErrorString(e);
+    return VFX_EHIP;
+  }
+  return VFX_OK;
+}
+
+int launch_near_f8(const Plan* p, int nrhs, int max_wgs, hipStream_t s, std::string& err) {
   const HostPlan& H = p->H;
   const DevicePlan& D = p->D;
   const DeviceTables& DT = p->ctx->D;
   const long total = (long)H.L * kF8N, sNY = (long)H.np_src.size() * kF8N;
-  // kF8Slices x L x n bytes per right-hand side fit the 4 x L x n bf16 slices' buffer
-  static_assert(kF8Slices <= 8, "leaf slices exceed the slice buffer");
   int8_t* xs = (int8_t*)D.xs;
-  hipLaunchKernelGGL(k_split_i8, dim3((H.L + 3) / 4, nrhs), dim3(256), 0, s, H.L, fe, xs, D.xs_exp);
   const F8List lr{(int)H.ml_cfg.size(), 1, D.ml_cfg, D.ml_first, D.ml_count, DT.f8_W, DT.f8_Wexp};
   const F8List dn{4 * (int)H.mt_cfg.size(), 4, D.mt_cfg, D.mt_first, D.mt_count, DT.f8_A, DT.f8_Aexp};
   const int items = lr.nitems + dn.nitems;

@@ -51,13 +51,14 @@ inline bool touch(int la, int ax, int ay, int lb, int bx, int by) {
 
 }  // namespace
 
-// List-1 pairs grouped for the near-field kernels: configuration-major, and
-// inside a configuration by precision class (modes 1, 2: sources at level >=
-// min_level are applied in mixed precision: the self operator densely, the
-// other configurations in their low-rank form, so a configuration without
-// one stays in FP64), then by target.  Tiles of <= 64
-// pairs go to the low-rank or the dense kernel of their class.  l1_slot maps
-// every per-target list-1 entry to its pair.
+// List 1 sorted for the near-field kernels.  FP64 pairs of the same level go
+// to the per-target table of the symmetric kernel; the others become pairs
+// with a row of their own, configuration-major, inside a configuration by
+// precision class (modes 1, 2: sources at level >= min_level are applied in
+// mixed precision: the self operator densely, the other configurations in
+// their low-rank form, so a configuration without one stays in FP64), then
+// by target.  Tiles of <= 64 pairs go to the FP64 or the mixed kernel of
+// their class.  l1_slot maps every per-target list-1 entry to its pair.
 int build_near_tiles(const Tables& T, HostPlan& H, int mode, int min_level, std::string& err) {
   const int L = H.L;
   const int N1 = H.l1_ptr[L];
@@ -70,54 +71,72 @@ int build_near_tiles(const Tables& T, HostPlan& H, int mode, int min_level, std:
     const int c = H.l1_cfg[e];
     return mode >= 1 && H.box_level[H.leaf_box[H.l1_src[e]]] >= min_level && (c == kNearSelf || T.lr_R[c] > 0);
   };
-  // counting sort on (configuration, class)
-  std::vector<int> cnt(2 * kNearConfigs + 1, 0);
-  for (int e = 0; e < N1; ++e) cnt[2 * H.l1_cfg[e] + (mixed(e) ? 1 : 0) + 1]++;
-  for (int g = 0; g < 2 * kNearConfigs; ++g) cnt[g + 1] += cnt[g];
-  H.np_src.assign(N1, 0);
-  H.np_tgt.assign(N1, 0);
-  H.l1_slot.assign(N1, 0);
-  std::vector<int> pos(cnt.begin(), cnt.end() - 1);
-  for (int leaf = 0; leaf < L; ++leaf)  // targets ascending inside each group
+  bool any_mixed = false;
+  for (int e = 0; e < N1 && !any_mixed; ++e) any_mixed = mixed(e);
+  // With the target-stationary near field selected (near_mode 1), FP64 at
+  // K = 16 (also precision modes 1, 2 when no pair is mixed) takes that path:
+  // every non-self pair's factor product by the table GEMM
+  // (configuration-major tiles of 64), then the per-target-group kernel; the
+  // self pairs only there
+  const bool ts = H.near_mode == 1 && !any_mixed && k16 && T.ts_ok;
+  auto sym = [&](int e) { return !ts && H.l1_cfg[e] < 9 && !mixed(e); };
+  // same-level FP64 pairs, by target
+  H.sy_tgt.clear();
+  H.sy_nb.clear();
+  H.sy_row.assign(L, -1);
+  static const int kPlace[9] = {8, 2, 6, 4, 0, 3, 7, 1, 5};  // configuration -> place in sy_nb
+  for (int leaf = 0; leaf < L; ++leaf)
     for (int e = H.l1_ptr[leaf]; e < H.l1_ptr[leaf + 1]; ++e) {
+      if (!sym(e)) continue;
+      if (H.sy_row[leaf] < 0) {
+        H.sy_row[leaf] = (int)H.sy_tgt.size();
+        H.sy_tgt.push_back(leaf);
+        H.sy_nb.push_back(-1);
+        H.sy_nb.insert(H.sy_nb.end(), 8, L);
+      }
+      H.sy_nb[9 * (size_t)H.sy_row[leaf] + kPlace[H.l1_cfg[e]]] = H.l1_src[e];
+    }
+  // the others: counting sort on (configuration, class)
+  std::vector<int> cnt(2 * kNearConfigs + 1, 0);
+  for (int e = 0; e < N1; ++e)
+    if (!sym(e)) cnt[2 * H.l1_cfg[e] + (mixed(e) ? 1 : 0) + 1]++;
+  for (int g = 0; g < 2 * kNearConfigs; ++g) cnt[g + 1] += cnt[g];
+  const int NP = cnt[2 * kNearConfigs];
+  H.np_src.assign(NP, 0);
+  H.np_tgt.assign(NP, 0);
+  H.l1_slot.assign(N1, -1);
+  H.y_ptr.assign(L + 1, 0);
+  H.y_slot.clear();
+  std::vector<int> pos(cnt.begin(), cnt.end() - 1);
+  for (int leaf = 0; leaf < L; ++leaf) {  // targets ascending inside each group
+    for (int e = H.l1_ptr[leaf]; e < H.l1_ptr[leaf + 1]; ++e) {
+      if (sym(e)) continue;
       const int s = pos[2 * H.l1_cfg[e] + (mixed(e) ? 1 : 0)]++;
       H.np_src[s] = H.l1_src[e];
       H.np_tgt[s] = leaf;
       H.l1_slot[e] = s;
+      H.y_slot.push_back(s);
     }
-  for (auto* v : {&H.nt_cfg, &H.nt_first, &H.nt_count, &H.nl_cfg, &H.nl_first, &H.nl_count, &H.mt_cfg,
-                  &H.mt_first, &H.mt_count, &H.ml_cfg, &H.ml_first, &H.ml_count})
+    H.y_ptr[leaf + 1] = (int)H.y_slot.size();
+  }
+  for (auto* v : {&H.nl_cfg, &H.nl_first, &H.nl_count, &H.mt_cfg, &H.mt_first, &H.mt_count, &H.ml_cfg, &H.ml_first,
+                  &H.ml_count})
     v->clear();
-  // With the target-stationary near field selected (near_mode 1), FP64 at
-  // K = 16 (also precision modes 1, 2 when no pair is mixed) takes that path: every non-self pair's factor product by the
-  // table GEMM (configuration-major tiles of 64), then the per-target-group
-  // kernel; the self pairs only there
-  bool any_mixed = false;
-  for (int e = 0; e < N1 && !any_mixed; ++e) any_mixed = mixed(e);
-  const bool ts = H.near_mode == 1 && !any_mixed && k16 && T.ts_ok;
   constexpr int kTile = 64;
   for (int c = 0; c < kNearConfigs; ++c) {
-    const bool lr = ts ? c != kNearSelf : (k16 && T.lr_R[c] > 0);
-    if (ts && !lr) continue;
+    if (ts && c == kNearSelf) continue;
     for (int cls = 0; cls < 2; ++cls) {
       const int g = 2 * c + cls;
-      std::vector<int>*cf, *fi, *co;
-      if (cls == 0) {
-        cf = lr ? &H.nl_cfg : &H.nt_cfg;
-        fi = lr ? &H.nl_first : &H.nt_first;
-        co = lr ? &H.nl_count : &H.nt_count;
-      } else {
-        cf = lr ? &H.ml_cfg : &H.mt_cfg;
-        fi = lr ? &H.ml_first : &H.mt_first;
-        co = lr ? &H.ml_count : &H.mt_count;
+      std::vector<int>*cf = &H.nl_cfg, *fi = &H.nl_first, *co = &H.nl_count;
+      if (cls == 1) {
+        cf = c != kNearSelf ? &H.ml_cfg : &H.mt_cfg;
+        fi = c != kNearSelf ? &H.ml_first : &H.mt_first;
+        co = c != kNearSelf ? &H.ml_count : &H.mt_count;
       }
-      // FP64 low-rank tiles of the fused kernel hold 32 pairs (it splits a
-      // tile's work over its four waves), the others 64
-      const int tile = (cls == 0 && lr && !ts) ? kTile / 2 : kTile;
-      for (int f = cnt[g]; f < cnt[g + 1]; f += tile) {
+      for (int f = cnt[g]; f < cnt[g + 1]; f += kTile) {
         cf->push_back(c);
         fi->push_back(f);
-        co->push_back(std::min(tile, cnt[g + 1] - f));
+        co->push_back(std::min(kTile, cnt[g + 1] - f));
       }
     }
   }
@@ -659,12 +678,6 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
   H.leaf_ids.clear();
   for (int i = 0; i < L; ++i)
     if (!zero_leaf[i]) H.leaf_ids.push_back(i);
-  const int NL0 = (int)H.leaf_ids.size();
-  for (int f = 0; f < NL0; f += 64) {
-    H.t0_cfg.push_back(0);
-    H.t0_first.push_back(f);
-    H.t0_count.push_back(std::min(64, NL0 - f));
-  }
 
   // ---- per-cut-leaf pseudo-inverses --------------------------------------
   const int nX = T.nX, nG = T.nG, Kb2 = T.Kbar * T.Kbar;

@@ -890,20 +890,30 @@ static void build_pascal(Tables& T) {
   // P2L as a real GEMM operand
   T.p2l_rows = 64 * ((2 * P + 63) / 64);
   const int R = T.p2l_rows;
-  T.p2l_gemm.assign((size_t)kP2LSlots * n * R, 0.0);
-  for (int s = 0; s < kP2LSlots; ++s)
-    for (int l = 0; l < P; ++l)
-      for (int j = 0; j < n; ++j) {
-        const size_t src = 2 * (((size_t)s * P + l) * n + j);
-        T.p2l_gemm[((size_t)s * n + j) * R + 2 * l] = T.p2l[src];
-        T.p2l_gemm[((size_t)s * n + j) * R + 2 * l + 1] = T.p2l[src + 1];
+  // the source's values enter a P2L row through its exterior moments: folded
+  // and projected as the pair operators of build_moments
+  {
+    const int K = T.K, H = K / 2, H2 = H * H, E = T.mom_E, SE = E / 4;
+    T.p2l_gemm.assign((size_t)kP2LSlots * 4 * E * R, 0.0);
+#pragma omp parallel for schedule(dynamic, 1)
+    for (int s = 0; s < kP2LSlots; ++s)
+      for (int q = 0; q < 4; ++q) {
+        const double sx = (q & 2) ? -1 : 1, sy = (q & 1) ? -1 : 1;
+        for (int r = 0; r < 2 * P; ++r) {
+          const double* src = &T.p2l[2 * ((size_t)s * P + r / 2) * n + (r & 1)];
+          for (int e = 0; e < E; ++e) {
+            long double acc = 0;
+            for (int k = 0; k < H2; ++k) {
+              const int a = k / H, b = k % H, a1 = K - 1 - a, b1 = K - 1 - b;
+              const long double v = ((long double)src[2 * (a * K + b)] + sy * src[2 * (a * K + b1)]) +
+                                    sx * ((long double)src[2 * (a1 * K + b)] + sy * src[2 * (a1 * K + b1)]);
+              acc += v * T.mom_V[((size_t)q * H2 + k) * E + e];
+            }
+            T.p2l_gemm[((((size_t)s * 4 + q) * SE + e % SE) * 4 + e / SE) * R + r] = (double)(acc / 4);
+          }
+        }
       }
-  T.p2m_gemm.assign((size_t)n * R, 0.0);
-  for (int k = 0; k < P; ++k)
-    for (int j = 0; j < n; ++j) {
-      T.p2m_gemm[(size_t)j * R + 2 * k] = T.p2m[2 * ((size_t)k * n + j)];
-      T.p2m_gemm[(size_t)j * R + 2 * k + 1] = T.p2m[2 * ((size_t)k * n + j) + 1];
-    }
+  }
   // M2P (list 3) as a real GEMM operand.  A list-3 box w of a leaf b in a
   // level-restricted tree is a child of a colleague of b that does not touch
   // b: one level finer, centre offset (ox, oy) h_w/2 with odd ox, oy in
@@ -931,6 +941,198 @@ static void build_pascal(Tables& T) {
       }
     }
   }
+}
+
+// Exterior moments of a leaf, and the near-field operators acting on them.
+//
+// A density q = Laplacian(phi) with phi = (1-x^2)^2 (1-y^2)^2 P(x, y) has no
+// potential outside its leaf (phi and its normal derivative vanish on the
+// edges), and for P of degree <= K-5 per variable q lies in the leaf's
+// tensor polynomials of degree <= K-1.  So of the K^2 values of a leaf only
+// 4E = K^2 - (K-4)^2 combinations, the exterior moments, act on any other
+// leaf or box, exactly.  Reflecting the leaf in its axes splits values and
+// moments into four parities q = 2 qx + qy (0 even, 1 odd), each with H^2 =
+// (K/2)^2 folded values
+//   fh_q(a, b) = f(a,b) + sy f(a,b') + sx f(a',b) + sx sy f(a',b'),
+// a, b < K/2, a' = K-1-a, sx = qx ? -1 : 1, and E = 2K - 4 moments
+// m_q = V_q fh_q, V_q an orthonormal basis of the complement of the folded
+// q's above.  The value at a node is 1/4 of the signed sum of the four
+// folded values.
+//   mom_V  [q][k][e]          V_q, k the folded node
+//   mom_T  [q][s][l][row]     V_q and the P2M rows of parity q as the operand
+//                             of the moment kernel, k = SH l + s (SH = H^2/4);
+//                             row e < E a moment, row E + u the real (q = 0,
+//                             2) or imaginary (1, 3) part of the multipole
+//                             coefficient 2u (q = 0, 3) or 2u + 1 (q = 1, 2)
+//   sym_T  [q][step][l][row]  folded near field of a target from its own
+//                             leaf and its eight same-level neighbours:
+//                             steps of the own leaf (k = SH l + s), then of
+//                             the edge neighbours in x (moments of parity
+//                             (0, qy), (1, qy); k = SE l + s, SE = E/4), in y
+//                             ((qx, 0), (qx, 1)) and of the corners (all four
+//                             parities), each for the neighbour in the
+//                             positive direction(s); the reflected one's
+//                             block is the same up to the sign sx(q) sx(p)
+//                             (and / or sy(q) sy(p))
+//   pair_T [c][p][s][l][i]    coarse and fine configurations c + 9: values at
+//                             the K^2 nodes from the moments of the source
+static void build_moments(Tables& T) {
+  const int K = T.K, n = T.n, H = K / 2, H2 = H * H, SH = H2 / 4, M = H - 2, E = H2 - M * M, SE = E / 4;
+  const int P = T.p + 1, PQ = (P + 1) / 2;
+  T.mom_E = E;
+  T.mom_rows = 16 * ((E + PQ + 15) / 16);
+  T.sym_rows = 16 * ((H2 + 15) / 16);
+  T.mom_V.assign((size_t)4 * H2 * E, 0.0);
+  typedef long double ld;
+  // phi_i = (1-x^2)^2 T_i and its second derivative at the K nodes
+  std::vector<ld> f0((size_t)std::max(K - 4, 0) * K), f2(f0.size());
+  for (int a = 0; a < K; ++a) {
+    const ld x = -std::cos((ld)(2 * a + 1) * (ld)M_PIl / (2 * K));
+    const ld w = (1 - x * x) * (1 - x * x), w1 = -4 * x * (1 - x * x), w2 = 12 * x * x - 4;
+    ld t0 = 1, t1 = x, d0 = 0, d1 = 1, e0 = 0, e1 = 0;  // T_i, T_i', T_i'' and the next ones
+    for (int i = 0; i < K - 4; ++i) {
+      f0[(size_t)i * K + a] = w * t0;
+      f2[(size_t)i * K + a] = w2 * t0 + 2 * w1 * d0 + w * e0;
+      const ld t2 = 2 * x * t1 - t0, d2 = 2 * t1 + 2 * x * d1 - d0, e2 = 4 * d1 + 2 * x * e1 - e0;
+      t0 = t1, t1 = t2, d0 = d1, d1 = d2, e0 = e1, e1 = e2;
+    }
+  }
+  for (int q = 0; q < 4; ++q) {
+    const int px = q >> 1, py = q & 1, nc = M * M;
+    std::vector<ld> A((size_t)H2 * std::max(nc, 1)), Q((size_t)H2 * H2, 0);  // column-major
+    for (int u = 0; u < M; ++u)
+      for (int v = 0; v < M; ++v) {
+        const int i = 2 * u + px, j = 2 * v + py;
+        ld nrm = 0;
+        ld* col = &A[(size_t)(u * M + v) * H2];
+        for (int a = 0; a < H; ++a)
+          for (int b = 0; b < H; ++b) {
+            col[a * H + b] = f2[(size_t)i * K + a] * f0[(size_t)j * K + b] + f0[(size_t)i * K + a] * f2[(size_t)j * K + b];
+            nrm += col[a * H + b] * col[a * H + b];
+          }
+        for (int k = 0; k < H2; ++k) col[k] /= std::sqrt(nrm);
+      }
+    // Householder QR with column pivoting; the last E columns of Q span the
+    // complement
+    std::vector<std::vector<ld>> refl;
+    std::vector<int> left(nc);
+    for (int c = 0; c < nc; ++c) left[c] = c;
+    for (int c = 0; c < nc; ++c) {
+      int best = c;
+      ld bn = -1;
+      for (int d = c; d < nc; ++d) {
+        ld s = 0;
+        for (int k = c; k < H2; ++k) s += A[(size_t)left[d] * H2 + k] * A[(size_t)left[d] * H2 + k];
+        if (s > bn) bn = s, best = d;
+      }
+      std::swap(left[c], left[best]);
+      std::vector<ld> v(H2, 0);
+      ld* col = &A[(size_t)left[c] * H2];
+      const ld nr = std::sqrt(bn);
+      for (int k = c; k < H2; ++k) v[k] = col[k];
+      v[c] += col[c] >= 0 ? nr : -nr;
+      ld vv = 0;
+      for (int k = c; k < H2; ++k) vv += v[k] * v[k];
+      for (int k = c; k < H2; ++k) v[k] *= std::sqrt(2 / vv);
+      for (int d = c; d < nc; ++d) {
+        ld* cd = &A[(size_t)left[d] * H2];
+        ld s = 0;
+        for (int k = c; k < H2; ++k) s += v[k] * cd[k];
+        for (int k = c; k < H2; ++k) cd[k] -= s * v[k];
+      }
+      refl.push_back(v);
+    }
+    for (int e = 0; e < E; ++e) {
+      std::vector<ld> y(H2, 0);
+      y[nc + e] = 1;
+      for (int c = nc - 1; c >= 0; --c) {
+        ld s = 0;
+        for (int k = c; k < H2; ++k) s += refl[c][k] * y[k];
+        for (int k = c; k < H2; ++k) y[k] -= s * refl[c][k];
+      }
+      for (int k = 0; k < H2; ++k) T.mom_V[((size_t)q * H2 + k) * E + e] = (double)y[k];
+    }
+  }
+  // moment operand with the P2M rows: a = sum_j p2m_j f_j with the folded
+  // values is (1/4) sum_q sum_k fold_q(p2m)_k fh_q,k, where fold_q sums p2m
+  // over the four images of k with their signs
+  T.mom_T.assign((size_t)4 * H2 * T.mom_rows, 0.0);
+  for (int q = 0; q < 4; ++q) {
+    const double sx = (q & 2) ? -1 : 1, sy = (q & 1) ? -1 : 1;
+    for (int k = 0; k < H2; ++k) {
+      const int a = k / H, b = k % H;
+      const int img[4] = {a * K + b, a * K + K - 1 - b, (K - 1 - a) * K + b, (K - 1 - a) * K + K - 1 - b};
+      double* row = &T.mom_T[((size_t)q * H2 + (size_t)(k % SH) * 4 + k / SH) * T.mom_rows];
+      for (int e = 0; e < E; ++e) row[e] = T.mom_V[((size_t)q * H2 + k) * E + e];
+      for (int u = 0; u < PQ; ++u) {
+        const int l = 2 * u + ((q == 1 || q == 2) ? 1 : 0), im = q & 1;
+        if (l >= P) continue;
+        const double* pm = &T.p2m[2 * (size_t)l * n];
+        row[E + u] = 0.25 * (pm[2 * img[0] + im] + sy * pm[2 * img[1] + im] + sx * pm[2 * img[2] + im] +
+                             sx * sy * pm[2 * img[3] + im]);
+      }
+    }
+  }
+  // rows of the folded operator: block (q <- p) of configuration c in terms
+  // of the unnormalised folded values (1/4 from the two foldings)
+  auto block = [&](int c, int q, int p, std::vector<double>& B) {  // [k][i]
+    B.assign((size_t)H2 * H2, 0.0);
+    const double* A = &T.near[(size_t)c * n * n];  // [j][i]
+    for (int k = 0; k < H2; ++k)
+      for (int i = 0; i < H2; ++i) {
+        const int ka = k / H, kb = k % H, ia = i / H, ib = i % H;
+        ld s = 0;
+        for (int u = 0; u < 4; ++u)
+          for (int w = 0; w < 4; ++w) {
+            const int j = ((u & 2) ? K - 1 - ka : ka) * K + ((u & 1) ? K - 1 - kb : kb);
+            const int t = ((w & 2) ? K - 1 - ia : ia) * K + ((w & 1) ? K - 1 - ib : ib);
+            const int sg = (((u & p & 2) >> 1) + (u & p & 1) + ((w & q & 2) >> 1) + (w & q & 1)) & 1;
+            s += (sg ? -1 : 1) * (ld)A[(size_t)j * n + t];
+          }
+        // the image sums of k and i count every node of the quadrant once
+        B[(size_t)k * H2 + i] = (double)(s / 16);
+      }
+  };
+  const int KS = SH + 8 * SE, R = T.sym_rows;
+  T.sym_T.assign((size_t)4 * KS * 4 * R, 0.0);
+  std::vector<double> B;
+  for (int q = 0; q < 4; ++q) {
+    block(kNearSelf, q, q, B);
+    for (int k = 0; k < H2; ++k)
+      for (int i = 0; i < H2; ++i)
+        T.sym_T[(((size_t)q * KS + k % SH) * 4 + k / SH) * R + i] = B[(size_t)k * H2 + i];
+    const int qx = q >> 1, qy = q & 1;
+    const int cfg[8] = {7, 7, 5, 5, 8, 8, 8, 8};
+    const int par[8] = {qy, 2 + qy, 2 * qx, 2 * qx + 1, 0, 1, 2, 3};
+    for (int g = 0; g < 8; ++g) {
+      const int p = par[g];
+      block(cfg[g], q, p, B);
+      for (int e = 0; e < E; ++e)
+        for (int i = 0; i < H2; ++i) {
+          ld s = 0;
+          for (int k = 0; k < H2; ++k) s += (ld)B[(size_t)k * H2 + i] * T.mom_V[((size_t)p * H2 + k) * E + e];
+          T.sym_T[(((size_t)q * KS + SH + g * SE + e % SE) * 4 + e / SE) * R + i] = (double)s;
+        }
+    }
+  }
+  T.pair_T.assign((size_t)24 * 4 * E * n, 0.0);
+#pragma omp parallel for schedule(dynamic, 1)
+  for (int c = 0; c < 24; ++c)
+    for (int p = 0; p < 4; ++p)
+      for (int e = 0; e < E; ++e) {
+        std::vector<ld> acc(n, 0);
+        for (int k = 0; k < H2; ++k)
+          for (int u = 0; u < 4; ++u) {
+            const int ka = k / H, kb = k % H;
+            const int j = ((u & 2) ? K - 1 - ka : ka) * K + ((u & 1) ? K - 1 - kb : kb);
+            const int sg = (((u & p & 2) >> 1) + (u & p & 1)) & 1;
+            const ld v = (sg ? -1 : 1) * (ld)T.mom_V[((size_t)p * H2 + k) * E + e] / 4;
+            const double* A = &T.near[((size_t)(9 + c) * n + j) * n];
+            for (int i = 0; i < n; ++i) acc[i] += v * A[i];
+          }
+        double* dst = &T.pair_T[((((size_t)c * 4 + p) * SE + e % SE) * 4 + e / SE) * n];
+        for (int i = 0; i < n; ++i) dst[i] = (double)acc[i];
+      }
 }
 
 void build_tables(Tables& T) {
@@ -961,6 +1163,7 @@ void build_tables(Tables& T) {
   build_near(T);
   build_near_lowrank(T);
   build_near_classes(T);
+  build_moments(T);
   build_p2l(T);
   build_pascal(T);
 }

@@ -96,6 +96,11 @@ struct Tables {
   // (v = 2^e sum_s q_s 2^(-6-7s), q_s integers of magnitude <= 64)
   std::vector<int8_t> f8_W, f8_Q, f8_A;
   std::vector<int> f8_Wexp, f8_Qexp, f8_Aexp;
+  // exterior moments and the near-field operators on them (build_moments):
+  // E moments per parity, padded operand rows of the moment and the
+  // same-level kernel
+  int mom_E = 0, mom_rows = 0, sym_rows = 0;
+  std::vector<double> mom_V, mom_T, sym_T, pair_T;
   std::vector<double> p2m;             // (p+1) x n complex, [k][j] (re,im)
   std::vector<double> l2p;             // n x (p+1) complex, [i][l]
   std::vector<double> m2m;             // 4 x (p+1) x (p+1) complex, [q][k][l]
@@ -116,12 +121,11 @@ struct Tables {
   std::vector<double> m2l_logd;                   // 49: log|d/h|
   std::vector<double> m2m_in, m2m_out;            // 4 x P complex: (2w)^-k, w^l
   std::vector<double> l2l_in, l2l_out;            // 4 x P complex: w^k, (2w)^-l
-  // P2L tables as real GEMM operands: [slot][j][row], row = 2l (re) or
-  // 2l+1 (im), rows padded to p2l_rows (a multiple of 64)
+  // P2L tables as real GEMM operands on the source's exterior moments:
+  // [slot][parity][step][l][row] (moment SE l + step), row = 2l (re) or 2l+1
+  // (im), rows padded to p2l_rows (a multiple of 64)
   int p2l_rows = 0;
   std::vector<double> p2l_gemm;
-  // P2M as a real GEMM operand: [j][row], rows as for P2L
-  std::vector<double> p2m_gemm;
   // M2P (list 3) as a real GEMM operand: [slot][k][i], k < p2l_rows
   std::vector<double> m2p_gemm;
   // Target-stationary near field (K = 16; ts_ok when every non-self class
@@ -154,9 +158,8 @@ struct DeviceTables {
   bool ready = false;
   int device = -1;
   double *t = nullptr, *tbar = nullptr, *w2 = nullptr, *AbarT = nullptr, *cbar = nullptr, *A = nullptr;
-  double *near = nullptr, *near_s2 = nullptr;
+  double *mom_T = nullptr, *sym_T = nullptr, *pair_T = nullptr;
   int* lr_R = nullptr;
-  double *lr_W = nullptr, *lr_Q = nullptr;
   uint16_t *fx_W = nullptr, *fx_Q = nullptr, *fx_A = nullptr;
   int *fx_Wexp = nullptr, *fx_Qexp = nullptr, *fx_Aexp = nullptr;
   int8_t *f8_W = nullptr, *f8_Q = nullptr, *f8_A = nullptr;
@@ -164,7 +167,7 @@ struct DeviceTables {
   double2 *p2m = nullptr, *l2p = nullptr, *m2m = nullptr, *l2l = nullptr, *m2l = nullptr, *p2l = nullptr;
   double* p2l_area = nullptr;
   double *pas_m2l = nullptr, *pas_m2m = nullptr, *pas_l2l = nullptr, *m2l_logd = nullptr, *p2l_gemm = nullptr;
-  double *p2m_gemm = nullptr, *m2p_gemm = nullptr;
+  double* m2p_gemm = nullptr;
   double *pas_m2l_t = nullptr, *pas_m2m_t = nullptr, *pas_l2l_t = nullptr;
   double2 *m2l_tpow = nullptr, *m2l_tneg = nullptr, *m2m_in = nullptr, *m2m_out = nullptr, *l2l_in = nullptr,
           *l2l_out = nullptr;
@@ -204,13 +207,17 @@ struct HostPlan {
   std::vector<int> dn_grp;                   // leaf groups of the downward kernel
   int up_slots = 0;
   std::vector<int> l4_ptr, l4_src, l4_cfg;   // per box (source leaves)
-  // list-1 pairs regrouped by table configuration (config-major, targets
-  // ascending inside a configuration) for the batched near-field GEMM;
-  // l1_slot maps each per-target list-1 entry to its pair index
-  std::vector<int> np_src, np_tgt, l1_slot;
-  std::vector<int> nt_cfg, nt_first, nt_count;  // dense GEMM tiles of <= 64 pairs
-  std::vector<int> nl_cfg, nl_first, nl_count;  // low-rank tiles of <= 64 pairs
-  // the same for the pairs applied in mixed precision (bf16 slices)
+  // same-level FP64 list-1 pairs: targets with at least one, their nine
+  // source leaves (own, +x, -x, +y, -y, ++, -+, +-, --; none: -1 for the own
+  // leaf, else L, the zero row of the moments) and the index of a leaf among them (-1 for none)
+  std::vector<int> sy_tgt, sy_nb, sy_row;
+  // the other list-1 pairs (in the target-stationary mode all of them)
+  // regrouped by table configuration, config-major, targets ascending inside
+  // a configuration; l1_slot maps each per-target list-1 entry to its pair
+  // index (-1 for none); y_ptr, y_slot: the pair rows of each target
+  std::vector<int> np_src, np_tgt, l1_slot, y_ptr, y_slot;
+  std::vector<int> nl_cfg, nl_first, nl_count;  // FP64 tiles of <= 64 pairs
+  // tiles of the pairs applied in mixed precision: self (mt), low rank (ml)
   std::vector<int> mt_cfg, mt_first, mt_count, ml_cfg, ml_first, ml_count;
   int precision = 0, mixed_min_level = 0;
   // target-stationary near field (FP64, K = 16): groups of kTsGroup
@@ -229,8 +236,7 @@ struct HostPlan {
   std::vector<int> p4_src, l4_slot, t4_cfg, t4_first, t4_count;
   // list-3 entries regrouped by M2P slot, the same way
   std::vector<int> p3_src, l3_slot, t3_cfg, t3_first, t3_count;
-  // P2M over all leaves as one GEMM configuration
-  std::vector<int> leaf_ids, t0_cfg, t0_first, t0_count;
+  std::vector<int> leaf_ids;                 // leaves with possibly nonzero data
   std::vector<int> cut_leaf;                 // ncut
   std::vector<int> owner;                    // L
   std::vector<int> ext_ptr, ext_tgt;         // per cut leaf (targets, itself first)
@@ -259,7 +265,10 @@ struct DevicePlan {
   int *anc_ptr = nullptr, *anc = nullptr, *anc_leaf = nullptr, *dn_grp = nullptr;
   double2* locf = nullptr;  // full local expansion of every leaf, L x (p+1)  // partial multipoles of split boxes, up_slots x (p+1)
   int *l4_ptr = nullptr, *l4_src = nullptr, *l4_cfg = nullptr;
-  int *np_src = nullptr, *l1_slot = nullptr, *nt_cfg = nullptr, *nt_first = nullptr, *nt_count = nullptr;
+  int *np_src = nullptr, *y_ptr = nullptr, *y_slot = nullptr, *sy_nb = nullptr, *sy_row = nullptr;
+  // exterior moments (L + 1 rows, row L stays zero), and the same-level near
+  // field of each target in folded form, one row per sy_tgt
+  double *mom = nullptr, *ysym = nullptr;
   int *nl_cfg = nullptr, *nl_first = nullptr, *nl_count = nullptr;
   int *mt_cfg = nullptr, *mt_first = nullptr, *mt_count = nullptr, *ml_cfg = nullptr, *ml_first = nullptr,
       *ml_count = nullptr;
@@ -272,7 +281,7 @@ struct DevicePlan {
   double* near_z = nullptr;  // target-stationary path: per-pair factor products Z, n_pairs x 64
   int *ts_grp = nullptr, *ts_tcls = nullptr, *ts_row = nullptr, *ts_code = nullptr;
   int *p4_src = nullptr, *l4_slot = nullptr, *t4_cfg = nullptr, *t4_first = nullptr, *t4_count = nullptr;
-  int *leaf_ids = nullptr, *t0_cfg = nullptr, *t0_first = nullptr, *t0_count = nullptr;
+  int* leaf_ids = nullptr;
   double* p2l_y = nullptr;   // per-entry P2L partial locals, n_list4 x p2l_rows
   int *p3_src = nullptr, *l3_slot = nullptr, *t3_cfg = nullptr, *t3_first = nullptr, *t3_count = nullptr;
   double* m2p_y = nullptr;   // per-entry M2P values at the target nodes, n_list3 x n
@@ -298,14 +307,14 @@ struct Plan {
   // after the extension; M2L waits for P2L (p2l_ev), the far-field kernel
   // for the whole side stream (join_ev)
   hipStream_t side = nullptr;
-  hipEvent_t fork_ev = nullptr, join_ev = nullptr, p2l_ev = nullptr, up_ev = nullptr;
+  hipEvent_t fork_ev = nullptr, join_ev = nullptr, p2l_ev = nullptr, up_ev = nullptr, mom_ev = nullptr;
   // per-phase timing: one set of kEvents events per timed execute
   static constexpr int kEvents = 14;
   // launch parameters chosen by vfx_plan_autotune
   struct Tune {
     int near_wgs = 512;  // work-group cap of the persistent near-field kernels (2 per CU,
                          // leaving room for the caller's stream beside them)
-    int dense_mtb = 4;   // row tiles per block of the dense near-field GEMM (K = 16)
+    int dense_mtb = 4;   // kept for the interface: no present kernel has row blocks to choose
   } tune;
   bool timing = false;
   std::vector<hipEvent_t> ev;   // kEvents * capacity
@@ -329,6 +338,15 @@ int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err);
 int launch_interp(Plan* p, const double* V, long npts, const double* px, const double* py, double* out,
                   hipStream_t s, std::string& err);
 int launch_net_charge(Plan* p, const double* fe, int nrhs, double* out, hipStream_t s, std::string& err);
+// doubles from one parity's E moments to the next: whole 128-byte lines
+__host__ __device__ constexpr int moment_stride(int E) { return (E + 15) / 16 * 16; }
+// near_sym.hip: exterior moments and P2M; FP64 list 1; P2L.  At K = 16 a work
+// item holds 64 targets where that makes at least kSymItems4 items, 32 where
+// those make kSymItems2, else 16.
+constexpr long kSymItems4 = 512, kSymItems2 = 256;
+int launch_moments(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err);
+int launch_near_sym(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err);
+int launch_p2l(const Plan* p, int nrhs, hipStream_t s, std::string& err);
 // ext_batch.hip: batches of at least this many right-hand sides compute
 // the extension's two matrix products (A1 per cut leaf, A2 over every cut
 // leaf and right-hand side) as FP64 MFMA GEMMs ahead of the extension kernel
@@ -336,10 +354,12 @@ constexpr int kExtGemmMinRhs = 8;
 int launch_ext_gemm(const Plan* p, const double* f_cut, int nrhs, hipStream_t s, std::string& err);
 int launch_ext_eval(const Plan* p, const double* f_cut, double* fe, int nrhs, hipStream_t s, std::string& err);
 // mixed.hip
-int launch_near_fx(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err);
+int launch_split_fx(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err);
+int launch_near_fx(const Plan* p, int nrhs, int max_wgs, hipStream_t s, std::string& err);
 // int8 slices per operand row of the mixed-precision near field (mode 2)
 constexpr int kF8Slices = 5;
-int launch_near_f8(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err);
+int launch_split_f8(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err);
+int launch_near_f8(const Plan* p, int nrhs, int max_wgs, hipStream_t s, std::string& err);
 // near.hip
 int launch_near_ts(const Plan* p, const double* fe, double* V, int nrhs, int max_wgs, hipStream_t s,
                    std::string& err);
