@@ -251,7 +251,7 @@ struct HostPlan {
 
 struct DevicePlan {
   bool ready = false;
-  int *box_level = nullptr, *box_child0 = nullptr, *box_leaf = nullptr, *box_parent = nullptr;
+  int *box_level = nullptr, *box_next = nullptr, *box_parent = nullptr;
   double *box_cx = nullptr, *box_cy = nullptr;
   int* leaf_box = nullptr;
   int8_t* kind = nullptr;
