@@ -1741,6 +1741,12 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
 #undef VFX_M2P
 }
 
+// leaves times right-hand sides from which the side stream pays (one MI355X,
+// one against two streams: 64 leaves 54 and 81-95 us, ten trees of 160 to 976
+// leaves in a graph 918 and 979 us, 2510 leaves 159 and 129 us, 3808 leaves
+// 100 and 101 us, 4207 leaves 155 and 145 us)
+constexpr long kTwoStreamLeaves = 1000;
+
 int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut, double* fe, double* V,
                    hipStream_t s, std::string& err) {
   Context* c = p->ctx;
@@ -1835,11 +1841,17 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   // persistent near-field grids are bounded (about two work-groups per CU,
   // looping over the tiles).  With a mixed near field the slices of f^e are
   // cut beside the moments, else the side stream starts after them.
+  // Small trees stay on the caller's stream: a wait between streams costs
+  // about 7 us, more than their near field takes beside the other kernels.
+  const bool one = !H.ts && (long)L * nrhs < kTwoStreamLeaves;
+  hipStream_t side = one ? s : p->side;
   const bool mixed = H.precision >= 1 && !H.ts && !(H.ml_cfg.empty() && H.mt_cfg.empty());
   if (mixed) {
-    VFX_HIP(hipEventRecord(p->fork_ev, s));
-    VFX_HIP(hipStreamWaitEvent(p->side, p->fork_ev, 0));
-    int rc = H.precision == 2 ? launch_split_f8(p, fe, nrhs, p->side, err) : launch_split_fx(p, fe, nrhs, p->side, err);
+    if (!one) {
+      VFX_HIP(hipEventRecord(p->fork_ev, s));
+      VFX_HIP(hipStreamWaitEvent(side, p->fork_ev, 0));
+    }
+    int rc = H.precision == 2 ? launch_split_f8(p, fe, nrhs, side, err) : launch_split_fx(p, fe, nrhs, side, err);
     if (rc) return rc;
   }
   // exterior moments and multipoles of the leaves
@@ -1847,17 +1859,19 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     int rc = launch_moments(p, fe, nrhs, s, err);
     if (rc) return rc;
   }
-  VFX_HIP(hipEventRecord(p->mom_ev, s));
-  VFX_HIP(hipStreamWaitEvent(p->side, p->mom_ev, 0));
+  if (!one) {
+    VFX_HIP(hipEventRecord(p->mom_ev, s));
+    VFX_HIP(hipStreamWaitEvent(side, p->mom_ev, 0));
+  }
   // P2L first on the side stream (M2L on the caller's stream waits for it),
   // then the near field
-  MARK(10, p->side);
+  MARK(10, side);
   if (H.nlev > 2) {
-    int rc = launch_p2l(p, nrhs, p->side, err);
+    int rc = launch_p2l(p, nrhs, side, err);
     if (rc) return rc;
   }
-  VFX_HIP(hipEventRecord(p->p2l_ev, p->side));
-  MARK(5, p->side);
+  if (!one) VFX_HIP(hipEventRecord(p->p2l_ev, side));
+  MARK(5, side);
   if (H.ts) {
     // target-stationary near field: the factor products Z = (W_b P_g^T) f
     // of every non-self pair (table GEMM over the configuration-major
@@ -1865,28 +1879,28 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     // leaf's list-1 table sum in V
     if (!H.nl_cfg.empty())
       launch_gemm<256, 4>((int)H.nl_cfg.size(), 4, D.nl_cfg, D.nl_first, D.nl_count, D.np_src, DT.lr_Wp, fe,
-                          D.near_z, p->side, p->tune.near_wgs, R, sFL, sNZ);
+                          D.near_z, side, p->tune.near_wgs, R, sFL, sNZ);
     VFX_HIP(hipGetLastError());
-    MARK(6, p->side);
+    MARK(6, side);
     {
-      int rc = launch_near_ts(p, fe, V, nrhs, p->tune.near_wgs, p->side, err);
+      int rc = launch_near_ts(p, fe, V, nrhs, p->tune.near_wgs, side, err);
       if (rc) return rc;
     }
   } else {
-    int rc = launch_near_sym(p, fe, nrhs, p->tune.near_wgs, p->side, err);
+    int rc = launch_near_sym(p, fe, nrhs, p->tune.near_wgs, side, err);
     if (rc) return rc;
-    MARK(6, p->side);
+    MARK(6, side);
     if (mixed) {
       // pairs in mixed precision: the low-rank and self products of the
       // fixed-point bf16 (mode 1) or int8 (mode 2) slices (FP64 results, rows
       // of the same buffer)
-      rc = H.precision == 2 ? launch_near_f8(p, nrhs, p->tune.near_wgs, p->side, err)
-                            : launch_near_fx(p, nrhs, p->tune.near_wgs, p->side, err);
+      rc = H.precision == 2 ? launch_near_f8(p, nrhs, p->tune.near_wgs, side, err)
+                            : launch_near_fx(p, nrhs, p->tune.near_wgs, side, err);
       if (rc) return rc;
     }
   }
   VFX_HIP(hipGetLastError());
-  MARK(7, p->side);
+  MARK(7, side);
   if (!H.up_grp.empty()) {
     const int ng = (int)H.up_grp.size() / 5;
 #define VFX_UP(PMV, EX)                                                                                            \
@@ -1914,16 +1928,18 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   MARK(2, s);
   // M2P for list 3 on the side stream, behind the near field, once the
   // upward pass is done; the side stream then joins the caller's
-  VFX_HIP(hipEventRecord(p->up_ev, s));
-  VFX_HIP(hipStreamWaitEvent(p->side, p->up_ev, 0));
-  MARK(13, p->side);
+  if (!one) {
+    VFX_HIP(hipEventRecord(p->up_ev, s));
+    VFX_HIP(hipStreamWaitEvent(side, p->up_ev, 0));
+  }
+  MARK(13, side);
   m2p_gemm(n, T.p2l_rows, 2 * P, (int)H.t3_cfg.size(), D.t3_cfg, D.t3_first, D.t3_count, D.p3_src, DT.m2p_gemm,
-           (const double*)D.mpole, D.m2p_y, p->side, R, 2 * sMP, sM3);
+           (const double*)D.mpole, D.m2p_y, side, R, 2 * sMP, sM3);
   VFX_HIP(hipGetLastError());
-  MARK(11, p->side);
-  VFX_HIP(hipEventRecord(p->join_ev, p->side));
+  MARK(11, side);
+  if (!one) VFX_HIP(hipEventRecord(p->join_ev, side));
   if (H.nlev > 2) {
-    VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
+    if (!one) VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
     const int ng = (int)H.m2l_grp.size() - 1;
     if (ng > 0) {
 #define VFX_M2L(PMV)                                                                                             \
@@ -1975,7 +1991,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   }
   VFX_HIP(hipGetLastError());
   MARK(4, s);
-  VFX_HIP(hipStreamWaitEvent(s, p->join_ev, 0));  // join
+  if (!one) VFX_HIP(hipStreamWaitEvent(s, p->join_ev, 0));  // join
   MARK(8, s);
 #define VFX_FAR(PMV, EX, NPLV, TSV)                                                                            \
   hipLaunchKernelGGL((k_far<PMV, EX, NPLV, TSV>), dim3(L, R), dim3(64), 0, s, T.K, P, T.root_size, D.leaf_box,      \
