@@ -928,185 +928,144 @@ __global__ void __launch_bounds__(64) k_down(int Prt, double root_size, const in
 }
 
 // -------------------------------------------------------------------------
-// Far field and the near-field reduction, one wave per leaf; lane l holds
-// the nodes l + 64j, j < NPL (NPL = ceil(K^2/64)): L2P of the leaf's full
-// local expansion by Horner in the scaled node position, the near field (the
-// folded row of the same-level sources, unfolded here, and the rows of the
-// other list-1 pairs) and the list-3 sums of the M2P products (in list
-// order, deterministic), and the log terms: log(h) a_0 of each list-1 source
-// and log(h/2) a_0 of each list-3 box.  Every per-leaf quantity (the local
-// expansion, the list slots) comes in with one vector load, lane k holding
-// item k, and is broadcast with readlane, so no step waits on a chain of
-// scalar loads.  One wave per leaf keeps the whole grid resident at once.
-// Each row of the per-pair and M2P products is read once, by its target's
-// wave: those loads are non-temporal.  (The kernels that write the rows use
-// plain stores, so that part of them is still in the last-level cache when
-// this kernel runs; non-temporal stores there measured slower.)
-typedef double vfx_d2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  const long long u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)u, l);
-  const int hi = __builtin_amdgcn_readlane((int)(u >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
+// Far field and the near-field reduction: V at every leaf's nodes from its
+// full local expansion (L2P), the near field (the row of the same-level
+// sources and the rows of the other FP64 list-1 pairs), the M2P rows of list
+// 3, all in list order (deterministic), and the log terms: log(h) a_0 of each
+// list-1 source and log(h/2) a_0 of each list-3 box.
+// Everything is summed in folded form (parity q = 2 qx + qy of a quadrant
+// node, values of its four images = signed sums): a lane holds one of the
+// H^2 = (K/2)^2 quadrant nodes, so a row is four coalesced loads, and L2P
+// needs the powers of one z per lane with real coefficients: with c = a + ib
+// and Re(c z^l) = a Re z^l - b Im z^l, the term l adds to parity 0 (a) and 3
+// (b) for even l, 2 (a) and 1 (b) for odd l.  That is a quarter of the
+// arithmetic of a Horner scheme per node, which took 78% of the vector
+// units' time (wedge workload: 39 us alone, now 28).  A wave serves 64 / H^2 leaves (K = 4,
+// 8) or one (K = 12, 16), whose coefficients are then wave-uniform.
+// NODE: rows in node order too, those of the mixed-precision pairs (y_slot
+// holds ~row) and the target-stationary sums (h^2 times the list-1 sum, left
+// in V; ts).
+// Each row is read once, by its target's wave: those loads are non-temporal.
+// (The kernels that write the rows use plain stores, so that part of them is
+// still in the last-level cache when this kernel runs; non-temporal stores
+// there measured slower.)
+struct FarArgs {
+  int L, P;
+  double root_size;
+  bool ts;
+  const int *leaf_box, *box_level;
+  const double* t;
+  const int *l3_ptr, *l3_src, *l3_slot;
+  const double* Y3;
+  const double2 *locf, *mpole;
+  const int *l1_ptr, *l1_srcbox, *sy_row;
+  const double* YS;
+  const int *y_ptr, *y_slot;
+  const double* Y;
+  double* V;
+  long slf, smp, sys, sny, sy3, sv;
+};
 
-template <int PM, bool EXACT, int NPL, bool NTS>
-__global__ void __launch_bounds__(64) k_far(int K, int Prt, double root_size, const int* __restrict__ leaf_box,
-                                            const int* __restrict__ box_level, const double* __restrict__ t,
-                                            const int* __restrict__ l3_ptr, const int* __restrict__ l3_src,
-                                            const int* __restrict__ l3_slot, const double* __restrict__ Y3,
-                                            const double2* __restrict__ locf, const double2* __restrict__ mpole,
-                                            const int* __restrict__ l1_ptr, const int* __restrict__ l1_srcbox,
-                                            const int* __restrict__ sy_row, const double* __restrict__ YS,
-                                            const int* __restrict__ y_ptr, const int* __restrict__ y_slot,
-                                            const double* __restrict__ Y, double* __restrict__ V, long slf, long smp,
-                                            long sys, long sny, long sy3, long sv) {
-  const int P = EXACT ? PM : Prt;  // <= 64
-  locf += blockIdx.y * slf;        // right-hand side blockIdx.y
-  mpole += blockIdx.y * smp;
-  YS += blockIdx.y * sys;
-  Y += blockIdx.y * sny;
-  Y3 += blockIdx.y * sy3;
-  V += blockIdx.y * sv;
-  const int n = K * K;
-  const int leaf = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int b = leaf_box[leaf];
-  const int lev = box_level[b];
-  const double h = box_side(root_size, lev);
-  // per-lane items: list-1 entry `lane` (at most one per configuration,
-  // fewer than 64), list-3 entry `lane` (at most 20), local coefficient `lane`
-  const int e0 = l1_ptr[leaf], n1 = l1_ptr[leaf + 1] - e0;
-  const int f0 = l3_ptr[leaf], n3 = l3_ptr[leaf + 1] - f0;
-  const int g0 = NTS ? 0 : y_ptr[leaf], ny = NTS ? 0 : y_ptr[leaf + 1] - g0;
-  const int my_slot = (!NTS && lane < ny) ? y_slot[g0 + lane] : 0;
-  const int srow = NTS ? -1 : sy_row[leaf];
-  const double my_a0 = lane < n1 ? mpole[(size_t)l1_srcbox[e0 + lane] * P].x : 0.0;
-  const int my_slot3 = lane < n3 ? l3_slot[f0 + lane] : 0;
-  const double my_b0 = lane < n3 ? mpole[(size_t)l3_src[f0 + lane] * P].x : 0.0;
-  const double2 my_c = (lev >= 2 && lane < P) ? locf[(size_t)leaf * P + lane] : double2{0.0, 0.0};
-  // lane l holds nodes 4l .. 4l+3 when K^2 = 256 (rows of the per-pair
-  // products are read with two 16-byte loads per lane), else l + 64j
-  int node[NPL];
-  double tx[NPL], ty[NPL], acc[NPL];
-#pragma unroll
-  for (int j = 0; j < NPL; ++j) {
-    const int nd = NPL == 4 ? 4 * lane + j : lane + 64 * j;
-    node[j] = nd < n ? nd : 0;
-    tx[j] = 0.5 * t[node[j] / K];
-    ty[j] = 0.5 * t[node[j] % K];
-  }
-  // near field (list 1) and M2P (list 3) sums, log terms
+template <int K, bool NODE>
+__global__ void __launch_bounds__(256) k_far(FarArgs A) {
+  constexpr int n = K * K, H = K / 2, H2 = H * H, LPW = H2 <= 16 ? 64 / H2 : 1;
+  const long r = blockIdx.y;  // right-hand side
+  const double2* __restrict__ locf = A.locf + r * A.slf;
+  const double2* __restrict__ mpole = A.mpole + r * A.smp;
+  const double* __restrict__ YS = A.YS + r * A.sys;
+  const double* __restrict__ Y = A.Y + r * A.sny;
+  const double* __restrict__ Y3 = A.Y3 + r * A.sy3;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = LPW > 1 ? lane / H2 : 0;
+  const int node = LPW > 1 ? lane % H2 : min(lane, H2 - 1);  // quadrant node
+  int leaf = LPW * (4 * blockIdx.x + w) + sub;
+  const bool act = leaf < A.L && (LPW > 1 || lane < H2);
+  if (LPW * (4 * (int)blockIdx.x + w) >= A.L) return;
+  leaf = min(leaf, A.L - 1);
+  const int b = A.leaf_box[leaf], lev = A.box_level[b];
+  const double h = box_side(A.root_size, lev);
+  const int e0 = A.l1_ptr[leaf], n1 = A.l1_ptr[leaf + 1] - e0;
+  const int f0 = A.l3_ptr[leaf], n3 = A.l3_ptr[leaf + 1] - f0;
+  const int g0 = NODE && A.ts ? 0 : A.y_ptr[leaf], ny = NODE && A.ts ? 0 : A.y_ptr[leaf + 1] - g0;
+  const int srow = NODE && A.ts ? -1 : A.sy_row[leaf];
+  // log terms: the lanes of a leaf take its sources in turn
+  double lg = 0.0, lg3 = 0.0;
   {
-    double yn[NPL], y3[NPL], lg = 0.0, lg3 = 0.0;
+    constexpr int G = LPW > 1 ? H2 : 64;
+    const int l0 = LPW > 1 ? node : lane;
+    for (int e = l0; e < n1; e += G) lg += mpole[(size_t)A.l1_srcbox[e0 + e] * A.P].x;
+    for (int e = l0; e < n3; e += G) lg3 += mpole[(size_t)A.l3_src[f0 + e] * A.P].x;
 #pragma unroll
-    for (int j = 0; j < NPL; ++j) yn[j] = y3[j] = 0.0;
-    if (NTS) {
-      // the target-stationary kernel left h^2 times the list-1 table sum in V
+    for (int o = 1; o < G; o <<= 1) {
+      lg += __shfl_xor(lg, o, G);
+      lg3 += __shfl_xor(lg3, o, G);
+    }
+  }
+  const double lh = log(h);
+  const int na = node / H, nb = node % H;
+  const int img[4] = {na * K + nb, na * K + K - 1 - nb, (K - 1 - na) * K + nb, (K - 1 - na) * K + K - 1 - nb};
+  double yn[4] = {0.0, 0.0, 0.0, 0.0}, y3[4] = {0.0, 0.0, 0.0, 0.0}, yv[4] = {0.0, 0.0, 0.0, 0.0};
+  if (srow >= 0) {
+    const double* y = YS + (size_t)srow * n + node;
 #pragma unroll
-      for (int j = 0; j < NPL; ++j) yn[j] = V[(size_t)leaf * n + node[j]];
-      for (int e = 0; e < n1; ++e) lg += readlane_d(my_a0, e);
+    for (int q = 0; q < 4; ++q) yn[q] = __builtin_nontemporal_load(y + q * H2);
+  }
+#pragma unroll 4
+  for (int e = 0; e < ny; ++e) {
+    const int slot = A.y_slot[g0 + e];
+    if (NODE && slot < 0) {
+      const double* y = Y + (size_t)~slot * n;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) yv[k] += __builtin_nontemporal_load(y + img[k]);
     } else {
-      if (srow >= 0) {
-        // same-level sources: the folded row, four parities of (K/2)^2
-        const int H = K / 2;
-        const double* ys = YS + (size_t)srow * n;
-        if constexpr (NPL == 4) {
-          const int a = lane >> 2, bb = 4 * (lane & 3);
-          const bool up = bb >= 8;
-          const double sx = a < 8 ? 1.0 : -1.0, sy = up ? -1.0 : 1.0;
-          const double* r = ys + 8 * (a < 8 ? a : 15 - a) + (up ? 12 - bb : bb);
-          double w[4] = {0.0, 0.0, 0.0, 0.0};
+      const double* y = Y + (size_t)slot * n + node;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double sg = ((q & 2) ? sx : 1.0) * ((q & 1) ? sy : 1.0);
-            const vfx_d2 u0 = *(const vfx_d2*)(r + 64 * q), u1 = *(const vfx_d2*)(r + 64 * q + 2);
-            w[0] += sg * u0.x;
-            w[1] += sg * u0.y;
-            w[2] += sg * u1.x;
-            w[3] += sg * u1.y;
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) yn[j] = up ? w[3 - j] : w[j];
-        } else {
-#pragma unroll
-          for (int j = 0; j < NPL; ++j) {
-            const int a = node[j] / K, b = node[j] % K;
-            const double sx = a < H ? 1.0 : -1.0, sy = b < H ? 1.0 : -1.0;
-            const double* r = ys + (a < H ? a : K - 1 - a) * H + (b < H ? b : K - 1 - b);
-            yn[j] = (r[0] + sy * r[H * H]) + sx * (r[2 * H * H] + sy * r[3 * H * H]);
-          }
-        }
-      }
-      for (int e = 0; e < n1; ++e) lg += readlane_d(my_a0, e);
-#pragma unroll 4
-      for (int e = 0; e < ny; ++e) {
-        const double* y = Y + (size_t)__builtin_amdgcn_readlane(my_slot, e) * n;
-        if constexpr (NPL == 4) {
-          const vfx_d2 u0 = __builtin_nontemporal_load((const vfx_d2*)(y + 4 * lane)),
-                       u1 = __builtin_nontemporal_load((const vfx_d2*)(y + 4 * lane + 2));
-          yn[0] += u0.x;
-          yn[1] += u0.y;
-          yn[2] += u1.x;
-          yn[3] += u1.y;
-        } else {
-#pragma unroll
-          for (int j = 0; j < NPL; ++j) yn[j] += y[node[j]];
-        }
-      }
+      for (int q = 0; q < 4; ++q) yn[q] += __builtin_nontemporal_load(y + q * H2);
     }
-#pragma unroll 4
-    for (int q = 0; q < n3; ++q) {
-      const double* y = Y3 + (size_t)__builtin_amdgcn_readlane(my_slot3, q) * n;
-      if constexpr (NPL == 4) {
-        const vfx_d2 u0 = __builtin_nontemporal_load((const vfx_d2*)(y + 4 * lane)),
-                     u1 = __builtin_nontemporal_load((const vfx_d2*)(y + 4 * lane + 2));
-        y3[0] += u0.x;
-        y3[1] += u0.y;
-        y3[2] += u1.x;
-        y3[3] += u1.y;
-      } else {
-#pragma unroll
-        for (int j = 0; j < NPL; ++j) y3[j] += y[node[j]];
-      }
-      lg3 += readlane_d(my_b0, q);
-    }
-    const double lh = log(h);
-    const double lt = lh * lg + (lh - kLn2) * lg3;
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) acc[j] = (NTS ? yn[j] : h * h * yn[j]) + y3[j] + lt;
   }
-  // L2P
+#pragma unroll 4
+  for (int e = 0; e < n3; ++e) {
+    const double* y = Y3 + (size_t)A.l3_slot[f0 + e] * n + node;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y3[q] += __builtin_nontemporal_load(y + q * H2);
+  }
+  const double h2 = h * h;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) y3[q] += h2 * yn[q];
+  y3[0] += lh * lg + (lh - kLn2) * lg3;
   if (lev >= 2) {
-    double ur[NPL], ui[NPL];
-    {
-      const double cx = readlane_d(my_c.x, P - 1), cy = readlane_d(my_c.y, P - 1);
-#pragma unroll
-      for (int j = 0; j < NPL; ++j) {
-        ur[j] = cx;
-        ui[j] = cy;
-      }
+    const double2* __restrict__ c = locf + (size_t)leaf * A.P;
+    const double zx = 0.5 * A.t[na], zy = 0.5 * A.t[nb];
+    double px = 1.0, py = 0.0;  // z^l
+    auto step = [&](int l, double& re, double& im) __attribute__((always_inline)) {
+      const double2 cl = c[l];
+      re += cl.x * px;
+      im -= cl.y * py;
+      const double t = px * zx - py * zy;
+      py = px * zy + py * zx;
+      px = t;
+    };
+    int l = 0;
+#pragma unroll 4
+    for (; l + 1 < A.P; l += 2) {
+      step(l, y3[0], y3[3]);
+      step(l + 1, y3[2], y3[1]);
     }
-#pragma unroll
-    for (int l = P - 2; l >= 0; --l) {
-      const double cx = readlane_d(my_c.x, l), cy = readlane_d(my_c.y, l);
-#pragma unroll
-      for (int j = 0; j < NPL; ++j) {
-        const double r = ur[j] * tx[j] - ui[j] * ty[j] + cx;
-        ui[j] = ur[j] * ty[j] + ui[j] * tx[j] + cy;
-        ur[j] = r;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < NPL; ++j) acc[j] += ur[j];
+    if (l < A.P) step(l, y3[0], y3[3]);
   }
-  if constexpr (NPL == 4) {
-    *(double2*)(V + (size_t)leaf * n + 4 * lane) = make_double2(kInv2Pi * acc[0], kInv2Pi * acc[1]);
-    *(double2*)(V + (size_t)leaf * n + 4 * lane + 2) = make_double2(kInv2Pi * acc[2], kInv2Pi * acc[3]);
-  } else {
+  if (act) {
+    double* V = A.V + r * A.sv + (size_t)leaf * n;
+    if (NODE && A.ts) {
 #pragma unroll
-    for (int j = 0; j < NPL; ++j)
-      if (lane + 64 * j < n) V[(size_t)leaf * n + lane + 64 * j] = kInv2Pi * acc[j];
+      for (int k = 0; k < 4; ++k) yv[k] = V[img[k]];
+    } else if (NODE) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) yv[k] *= h2;
+    }
+    const double ep = y3[0] + y3[1], em = y3[0] - y3[1], op = y3[2] + y3[3], om = y3[2] - y3[3];
+    const double v[4] = {ep + op, em + om, ep - op, em - om};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) V[img[k]] = kInv2Pi * (NODE ? v[k] + yv[k] : v[k]);
   }
 }
 
@@ -1415,6 +1374,23 @@ static std::vector<double2> as_complex(const std::vector<double>& src) {
   return o;
 }
 
+// Rows of K^2 target nodes in folded form: y_q of a quadrant node is a quarter
+// of the signed sum of its four images (q = 2 qx + qy).
+static std::vector<double> fold_rows(const std::vector<double>& v, int K) {
+  const int n = K * K, H = K / 2, H2 = H * H;
+  std::vector<double> o(v.size());
+  for (size_t r = 0; r + n <= v.size(); r += n)
+    for (int i = 0; i < H2; ++i) {
+      const int a = i / H, b = i % H, a1 = K - 1 - a, b1 = K - 1 - b;
+      const long double y0 = v[r + a * K + b], y1 = v[r + a * K + b1], y2 = v[r + a1 * K + b], y3 = v[r + a1 * K + b1];
+      o[r + i] = (double)((y0 + y1 + y2 + y3) / 4);
+      o[r + H2 + i] = (double)((y0 - y1 + y2 - y3) / 4);
+      o[r + 2 * H2 + i] = (double)((y0 + y1 - y2 - y3) / 4);
+      o[r + 3 * H2 + i] = (double)((y0 - y1 - y2 + y3) / 4);
+    }
+  return o;
+}
+
 int upload_tables(Context* c, std::string& err) {
   const Tables& T = c->T;
   DeviceTables& D = c->D;
@@ -1427,7 +1403,8 @@ int upload_tables(Context* c, std::string& err) {
   UP(D.cbar, T.cbar);
   UP(D.mom_T, T.mom_T);
   UP(D.sym_T, T.sym_T);
-  UP(D.pair_T, T.pair_T);
+  const std::vector<double> pair_f = fold_rows(T.pair_T, T.K), m2p_f = fold_rows(T.m2p_gemm, T.K);
+  UP(D.pair_T, pair_f);
   UP(D.lr_R, T.lr_R);
   UP(D.fx_W, T.fx_W);
   UP(D.fx_Wexp, T.fx_Wexp);
@@ -1448,7 +1425,7 @@ int upload_tables(Context* c, std::string& err) {
   UP(D.f8_A, T.f8_A);
   UP(D.f8_Aexp, T.f8_Aexp);
   UP(D.p2l_gemm, T.p2l_gemm);
-  UP(D.m2p_gemm, T.m2p_gemm);
+  UP(D.m2p_gemm, m2p_f);
   UP(D.pas_m2l, T.pas_m2l);
   UP(D.pas_m2l_t, T.pas_m2l_t);
   UP(D.pas_m2m_t, T.pas_m2m_t);
@@ -1993,33 +1970,24 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   MARK(4, s);
   if (!one) VFX_HIP(hipStreamWaitEvent(s, p->join_ev, 0));  // join
   MARK(8, s);
-#define VFX_FAR(PMV, EX, NPLV, TSV)                                                                            \
-  hipLaunchKernelGGL((k_far<PMV, EX, NPLV, TSV>), dim3(L, R), dim3(64), 0, s, T.K, P, T.root_size, D.leaf_box,      \
-                     D.box_level, DT.t, D.l3_ptr, D.l3_src, D.l3_slot, D.m2p_y, D.locf, D.mpole, D.l1_ptr,         \
-                     D.l1_srcbox, D.sy_row, D.ysym, D.y_ptr, D.y_slot, D.near_y, V, sLF, sMP, sYS, sNY, sM3, sFL)
-#define VFX_FAR_N(PMV, EX)      \
-  if (npl == 4 && H.ts)         \
-    VFX_FAR(PMV, EX, 4, true);  \
-  else if (npl == 4)            \
-    VFX_FAR(PMV, EX, 4, false); \
-  else if (npl == 3)            \
-    VFX_FAR(PMV, EX, 3, false); \
-  else                          \
-    VFX_FAR(PMV, EX, 1, false);
-  const int npl = (n + 63) / 64;  // 1, 3 or 4 for K = 4, 8, 12, 16
-  if (P == 21) {
-    VFX_FAR_N(21, true)
-  } else if (P == 25) {
-    VFX_FAR_N(25, true)
-  } else if (P == 31) {
-    VFX_FAR_N(31, true)
-  } else if (P == 41) {
-    VFX_FAR_N(41, true)
-  } else {
-    VFX_FAR_N(64, false)
-  }
-#undef VFX_FAR_N
+  {
+    const FarArgs A{L,      P,        T.root_size, H.ts,     D.leaf_box,   D.box_level, DT.t,    D.l3_ptr, D.l3_src,
+                    D.l3_slot, D.m2p_y, D.locf,  D.mpole, D.l1_ptr, D.l1_srcbox, D.sy_row, D.ysym, D.y_ptr,
+                    D.y_slot, D.near_y, V,       sLF,     sMP,      sYS,         sNY,     sM3,      sFL};
+    const bool node = H.ts || mixed;
+#define VFX_FAR(KV, LPWV)                                                                              \
+  if (node)                                                                                            \
+    hipLaunchKernelGGL((k_far<KV, true>), dim3((L + 4 * LPWV - 1) / (4 * LPWV), R), dim3(256), 0, s, A); \
+  else                                                                                                 \
+    hipLaunchKernelGGL((k_far<KV, false>), dim3((L + 4 * LPWV - 1) / (4 * LPWV), R), dim3(256), 0, s, A)
+    switch (T.K) {
+      case 4: VFX_FAR(4, 16); break;
+      case 8: VFX_FAR(8, 4); break;
+      case 12: VFX_FAR(12, 1); break;
+      default: VFX_FAR(16, 1); break;
+    }
 #undef VFX_FAR
+  }
   VFX_HIP(hipGetLastError());
   MARK(9, s);
   if (timed) p->n_timed++;

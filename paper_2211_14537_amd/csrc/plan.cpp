@@ -115,7 +115,7 @@ int build_near_tiles(const Tables& T, HostPlan& H, int mode, int min_level, std:
       H.np_src[s] = H.l1_src[e];
       H.np_tgt[s] = leaf;
       H.l1_slot[e] = s;
-      H.y_slot.push_back(s);
+      H.y_slot.push_back(mixed(e) ? ~s : s);
     }
     H.y_ptr[leaf + 1] = (int)H.y_slot.size();
   }

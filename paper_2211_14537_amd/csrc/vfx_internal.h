@@ -214,7 +214,8 @@ struct HostPlan {
   // the other list-1 pairs (in the target-stationary mode all of them)
   // regrouped by table configuration, config-major, targets ascending inside
   // a configuration; l1_slot maps each per-target list-1 entry to its pair
-  // index (-1 for none); y_ptr, y_slot: the pair rows of each target
+  // index (-1 for none); y_ptr, y_slot: the pair rows of each target (~row for
+  // a mixed-precision pair, whose row is in node order; the others are folded)
   std::vector<int> np_src, np_tgt, l1_slot, y_ptr, y_slot;
   std::vector<int> nl_cfg, nl_first, nl_count;  // FP64 tiles of <= 64 pairs
   // tiles of the pairs applied in mixed precision: self (mt), low rank (ml)
