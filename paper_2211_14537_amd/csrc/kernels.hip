@@ -47,14 +47,19 @@ __device__ __forceinline__ double wave_sum(double v) {
 __device__ __forceinline__ double box_side(double root, int level) { return ldexp(root, -level); }
 
 // -------------------------------------------------------------------------
-// Extension of one cut leaf per work-group (256 threads): f_G = P_i f_I
+// Extension of one cut leaf per work-group (NT threads): f_G = P_i f_I
 // (A1), values on the Kbar x Kbar grid of Sbar (given data at interior
 // nodes, A_{Xbar,G} f_G elsewhere; A2), the total-order Chebyshev
 // coefficients (A3) and their values on the K x K nodes of every target
 // leaf.  Every global load whose address is known early is issued at the
 // start (two waves: indices/geometry, then the data they point to), so the
-// work-group's critical path holds few memory round trips.
+// work-group's critical path holds few memory round trips.  The time of one
+// work-group is the time of the phase on small trees: with at most one cut
+// leaf per CU it has 1024 threads (A1 in one pass, four targets at a time),
+// with at most two 512; more cut leaves run at 256, six work-groups per CU,
+// where the HBM stream of the operators is the bound.
 constexpr int kExtTgtMax = 16;  // targets whose geometry is staged in LDS
+constexpr int kExtOnePerCu = 256;  // 64 leaves, 20 cut: 54.4 -> 47.7 us; ten small trees: 889 -> 834 us
 
 // f^e of the leaves no extension list writes, 16-byte pieces e0, e0 +
 // step, ... below e1 (piece e: right-hand side e / half, element 2 (e mod
@@ -84,7 +89,8 @@ __device__ __forceinline__ void fe_init_range(long e0, long e1, long step, int n
   }
 }
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k_extension(
+template <int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 ? 6 : 4))) k_extension(
     int K, int Kb, int nX, int nG, const int* __restrict__ pinv_ptr, const uint16_t* __restrict__ pinv_idx,
     const double* __restrict__ pinv_val, const uint8_t* __restrict__ sbar_given, const int* __restrict__ ext_ptr,
     const int* __restrict__ ext_tgt, const double* __restrict__ ext_geo, const double* __restrict__ t,
@@ -109,10 +115,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   __shared__ double s_fG[kMaxG];
   __shared__ double s_cb[kMaxKb * kMaxKb];
   __shared__ double s_g[kMaxKb * kMaxKb];
-  __shared__ double s_tmp[kMaxKb * kMaxKb];
   __shared__ double s_coef[kMaxKb * kMaxKb];
-  __shared__ double s_Ex[kMaxK * kMaxKb];
-  __shared__ double s_Ey[kMaxK * kMaxKb];
+  // targets evaluated side by side, 256 threads each
+  constexpr int TQ = NT / 256, TB = kMaxK * kMaxKb;
+  __shared__ double s_tmpq[TQ * TB], s_Exq[TQ * TB], s_Eyq[TQ * TB];
+  double* const s_tmp = s_tmpq;
   __shared__ double s_t[kMaxK];
   __shared__ double s_geo[3 * kExtTgtMax];
   __shared__ int s_tg[kExtTgtMax];
@@ -124,9 +131,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   const int off = pinv_ptr[c], ni = pinv_ptr[c + 1] - off;
   const int e0 = ext_ptr[c], ne = ext_ptr[c + 1] - e0;
   const double* fc = f_cut + (size_t)c * nX;
+  // A2's operator does not wait for anything: with threads to spare, thread
+  // (a, hf) takes the even (hf = 0) or odd rows of one Sbar point into
+  // registers now (the default stencil of 66 support nodes)
+  const bool early = NT > 256 && nG == 66;
+  const int hf = tid / Kb2, ga = tid - hf * Kb2;
+  double wA[NT > 256 ? 34 : 1];
+  if constexpr (NT > 256) {
+    if (early && hf < 2) {
+#pragma unroll
+      for (int u = 0; u < 32; ++u) wA[u] = AbarT[(size_t)(2 * u + hf) * Kb2 + ga];
+      wA[32] = AbarT[(size_t)64 * Kb2 + ga];
+      wA[33] = AbarT[(size_t)65 * Kb2 + ga];
+    }
+  }
   // first load wave: indices, flags, small tables, target geometry
   int idx0 = tid < ni ? pinv_idx[off + tid] : 0;
-  int idx1 = tid + 256 < ni ? pinv_idx[off + tid + 256] : 0;
+  int idx1 = tid + NT < ni ? pinv_idx[off + tid + NT] : 0;
   const bool given = tid < Kb2 && sbar_given[(size_t)c * Kb2 + tid];
   if (tid < Kb2) s_cb[tid] = cbar[tid];
   if (tid < K) s_t[tid] = t[tid];
@@ -138,15 +159,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   }
   // second load wave: interior samples and the given Sbar-grid values
   if (tid < ni) s_fI[tid] = fc[idx0];
-  if (tid + 256 < ni) s_fI[tid + 256] = fc[idx1];
-  for (int q = tid + 512; q < ni; q += blockDim.x) s_fI[q] = fc[pinv_idx[off + q]];
+  if (tid + NT < ni) s_fI[tid + NT] = fc[idx1];
+  for (int q = tid + 2 * NT; q < ni; q += NT) s_fI[q] = fc[pinv_idx[off + q]];
   if (tid < Kb2) {
     s_given[tid] = given;
     if (given) s_g[tid] = fc[n + tid];
   }
   __syncthreads();
-  // A1: f_G = P_i f_I  (P_i: nG x ni row-major).  Wave w takes rows
-  // 16w..16w+15 in four passes of 4, lane l the columns l, l + 64, l + 128,
+  // A1: f_G = P_i f_I  (P_i: nG x ni row-major).  Wave w takes 4096 / NT rows
+  // in passes of 4, lane l the columns l, l + 64, l + 128,
   // l + 192 (then l + 256, ... for ni > 256): one pass reads four whole rows
   // (ni <= 256), every load of a wave 512 contiguous bytes, 16 loads in
   // flight at once.  The 4 row partials are combined across the lanes by a
@@ -158,9 +179,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   // (they do not displace the data the later kernels reuse).
   const double* P = pinv_val + (size_t)off * nG;
 #pragma unroll 1
-  for (int pass = 0; pass < 4; ++pass) {
+  for (int pass = 0; pass < 1024 / NT; ++pass) {
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const int r0 = 16 * wave + 4 * pass;
+    const int r0 = 4096 / NT * wave + 4 * pass;
 #pragma unroll 1
     for (int q = lane; q < ni; q += 256) {
       double f[4], p[4][4];
@@ -193,7 +214,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     for (int o = 4; o < 64; o <<= 1) acc[0] += __shfl_xor(acc[0], o, 64);
     if (lane < 4 && r0 + lane < nG) s_fG[r0 + lane] = acc[0];
   }
-  for (int r = 64 + wave; r < nG; r += blockDim.x / 64) {
+  for (int r = 64 + wave; r < nG; r += NT / 64) {
     double a = 0.0;
     const double* pr = P + (size_t)r * ni;
     for (int q = lane; q < ni; q += 64) a += pr[q] * s_fI[q];
@@ -203,7 +224,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   __syncthreads();
   // A2: the Sbar grid values not given as data, A_{Xbar,G} f_G (universal
   // operator rows in batches of 16 independent loads)
-  for (int a = tid; a < Kb2; a += blockDim.x) {
+  if constexpr (NT > 256) {
+    if (early) {
+      if (hf < 2) {  // the sums of the general path below, its two halves apart
+        double v = 0.0;
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v = __builtin_fma(wA[u], s_fG[2 * u + hf], v);
+        if (hf == 0) {
+          v = __builtin_fma(wA[32], s_fG[64], v);
+          v = __builtin_fma(wA[33], s_fG[65], v);
+        }
+        s_tmp[tid] = v;
+      }
+      __syncthreads();
+      if (tid < Kb2 && !s_given[tid]) s_g[tid] = s_tmp[tid] + s_tmp[Kb2 + tid];
+    }
+  }
+  for (int a = tid; a < Kb2 && !early; a += NT) {
     if (s_given[a]) continue;
     double v0 = 0.0, v1 = 0.0;
     int r = 0;
@@ -222,14 +259,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
   }
   __syncthreads();
   // A3: coefficients c = C g C^T, truncated to total order < Kbar
-  for (int e = tid; e < Kb2; e += blockDim.x) {
+  for (int e = tid; e < Kb2; e += NT) {
     const int m = e / Kb, j = e % Kb;
     double acc = 0.0;
     for (int i = 0; i < Kb; ++i) acc += s_cb[m * Kb + i] * s_g[i * Kb + j];
     s_tmp[e] = acc;
   }
   __syncthreads();
-  for (int e = tid; e < Kb2; e += blockDim.x) {
+  for (int e = tid; e < Kb2; e += NT) {
     const int m = e / Kb, nn = e % Kb;
     double acc = 0.0;
     if (m + nn < Kb)
@@ -237,26 +274,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
     s_coef[e] = acc;
   }
   __syncthreads();
-  // values at the K x K nodes of every target leaf (the cut leaf first)
-  for (int q = 0; q < ne; ++q) {
-    int j;
-    double ox, oy, sc;
-    if (q < kExtTgtMax) {
-      j = s_tg[q];
-      ox = s_geo[3 * q];
-      oy = s_geo[3 * q + 1];
-      sc = s_geo[3 * q + 2];
-    } else {
-      j = ext_tgt[e0 + q];
-      ox = ext_geo[3 * (e0 + q)];
-      oy = ext_geo[3 * (e0 + q) + 1];
-      sc = ext_geo[3 * (e0 + q) + 2];
+  // values at the K x K nodes of every target leaf (the cut leaf first), TQ
+  // targets at a time
+  const int sub = wave / 4, st = tid & 255;
+  double *tq = s_tmpq + sub * TB, *Ex = s_Exq + sub * TB, *Ey = s_Eyq + sub * TB;
+  for (int q0 = 0; q0 < ne; q0 += TQ) {
+    const int q = q0 + sub;
+    int j = 0;
+    double ox = 0.0, oy = 0.0, sc = 0.0;
+    if (q < ne) {
+      if (q < kExtTgtMax) {
+        j = s_tg[q];
+        ox = s_geo[3 * q];
+        oy = s_geo[3 * q + 1];
+        sc = s_geo[3 * q + 2];
+      } else {
+        j = ext_tgt[e0 + q];
+        ox = ext_geo[3 * (e0 + q)];
+        oy = ext_geo[3 * (e0 + q) + 1];
+        sc = ext_geo[3 * (e0 + q) + 2];
+      }
     }
-    if (tid < 2 * K) {
-      const int a = tid % K;
-      const bool isy = tid >= K;
+    if (st < 2 * K) {
+      const int a = st % K;
+      const bool isy = st >= K;
       const double xi = (isy ? oy : ox) + sc * s_t[a];
-      double* dst = (isy ? s_Ey : s_Ex) + a * Kb;
+      double* dst = (isy ? Ey : Ex) + a * Kb;
       double t0 = 1.0, t1 = xi;
       dst[0] = 1.0;
       if (Kb > 1) dst[1] = xi;
@@ -268,19 +311,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) k
       }
     }
     __syncthreads();
-    for (int idx = tid; idx < Kb * K; idx += blockDim.x) {
+    for (int idx = st; idx < Kb * K; idx += 256) {
       const int m = idx / K, b = idx % K;
       double acc = 0.0;
-      for (int nn = 0; nn < Kb - m; ++nn) acc += s_coef[m * Kb + nn] * s_Ey[b * Kb + nn];
-      s_tmp[idx] = acc;
+      for (int nn = 0; nn < Kb - m; ++nn) acc += s_coef[m * Kb + nn] * Ey[b * Kb + nn];
+      tq[idx] = acc;
     }
     __syncthreads();
-    for (int idx = tid; idx < n; idx += blockDim.x) {
-      const int a = idx / K, b = idx % K;
-      double acc = 0.0;
-      for (int m = 0; m < Kb; ++m) acc += s_Ex[a * Kb + m] * s_tmp[m * K + b];
-      fe[(size_t)j * n + idx] = acc;
-    }
+    if (q < ne)
+      for (int idx = st; idx < n; idx += 256) {
+        const int a = idx / K, b = idx % K;
+        double acc = 0.0;
+        for (int m = 0; m < Kb; ++m) acc += Ex[a * Kb + m] * tq[m * K + b];
+        fe[(size_t)j * n + idx] = acc;
+      }
     __syncthreads();
   }
 }
@@ -1795,7 +1839,6 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     // initialisation of the other leaves
     const int ext_blocks = H.ncut * nrhs;
     const long pieces = (long)L * n / 2 * nrhs;
-    const int copy_blocks = (int)std::min<long>((pieces + 255) / 256, 1024);
     // a batch of at least kExtGemmMinRhs right-hand sides: A1 and A2 as
     // MFMA GEMMs, then the Chebyshev step and the evaluation for eight
     // right-hand sides per work-group; the extension kernel only
@@ -1807,9 +1850,19 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
       if (rc) return rc;
     }
     const int blocks1 = gemm ? 0 : ext_blocks;
-    hipLaunchKernelGGL(k_extension, dim3(blocks1 + copy_blocks), dim3(256), 0, s, T.K, T.Kbar, T.nX, T.nG,
-                       D.pinv_ptr, D.pinv_idx, D.pinv_val, D.sbar_given, D.ext_ptr, D.ext_tgt, D.ext_geo, DT.t,
-                       DT.AbarT, DT.cbar, f_cut, fe, nrhs, sFC, sFL, blocks1, L, D.fe_src, f_leaf);
+    const int nt = blocks1 > 0 && blocks1 <= kExtOnePerCu ? 1024 : blocks1 > 0 && blocks1 <= 2 * kExtOnePerCu ? 512 : 256;
+    const int copy_blocks = (int)std::min<long>((pieces + nt - 1) / nt, 262144 / nt);
+#define VFX_EXT(NTV)                                                                                               \
+  hipLaunchKernelGGL(k_extension<NTV>, dim3(blocks1 + copy_blocks), dim3(NTV), 0, s, T.K, T.Kbar, T.nX, T.nG,      \
+                     D.pinv_ptr, D.pinv_idx, D.pinv_val, D.sbar_given, D.ext_ptr, D.ext_tgt, D.ext_geo, DT.t,      \
+                     DT.AbarT, DT.cbar, f_cut, fe, nrhs, sFC, sFL, blocks1, L, D.fe_src, f_leaf)
+    if (nt == 1024)
+      VFX_EXT(1024);
+    else if (nt == 512)
+      VFX_EXT(512);
+    else
+      VFX_EXT(256);
+#undef VFX_EXT
   }
   VFX_HIP(hipGetLastError());
   MARK(1, s);
