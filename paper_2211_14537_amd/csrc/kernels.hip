@@ -341,6 +341,16 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
   return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 
+// calls f(integral_constant<int, I>) for I = I0 .. N-1 (ring indices in an
+// unrolled pipeline stay compile-time constants)
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
 // Per-output rows of the lane-per-pair kernels' LDS staging: 65 (not 64)
 // double2 apart, so the eight lanes of a segment that read the same entry
 // of eight outputs fall in different banks.
@@ -478,8 +488,9 @@ __global__ void __launch_bounds__(64) k_m2l_pairs(int P, double root_size, const
 // Lane e holds s_k = (-t)^k a_k of its source; for each output l it forms
 // t^l sum_k C(k+l-1,l) s_k (minus a_0 t^l/l; plus a_0 (log|d/h| + log h) for
 // l = 0).  Per-target sums go through LDS in chunks of 8 outputs, in entry
-// order (deterministic), together with the P2L contributions.
-template <int P>
+// order (deterministic), together with the P2L contributions.  SPLIT (small trees, whose groups leave SIMDs empty): one
+// work-group per chunk of outputs, each forming the s_k again.
+template <int P, bool SPLIT>
 __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* __restrict__ grp,
                                                   const int* __restrict__ box_level, const int* __restrict__ l2_ptr,
                                                   const int* __restrict__ l2_src, const int* __restrict__ l2_off,
@@ -528,9 +539,11 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
   const int bb = b0 + seg;
   const bool own = bb < b1;
   int r0 = 0, r1 = 0;
-  double p2r[NC], p2i[NC];
+  constexpr int NP = SPLIT ? 1 : NC;  // chunks this work-group forms
+  const int c0 = SPLIT ? (int)blockIdx.z : 0;
+  double p2r[NP], p2i[NP];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) p2r[c] = p2i[c] = 0.0;
+  for (int c = 0; c < NP; ++c) p2r[c] = p2i[c] = 0.0;
   if (own) {
     r0 = l2_ptr[bb] - e0;
     r1 = l2_ptr[bb + 1] - e0;
@@ -541,17 +554,24 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
     for (int q = q0; q < q1; ++q) {
       const double* y = p2l_y + (size_t)l4_slot[q] * p2l_rows + 2 * lc;
 #pragma unroll
-      for (int c = 0; c < NC; ++c)
-        if (8 * c + lc < P) {
-          p2r[c] += h2 * y[16 * c];
-          p2i[c] += h2 * y[16 * c + 1];
+      for (int c = 0; c < NP; ++c)
+        if (8 * (c0 + c) + lc < P) {
+          p2r[c] += h2 * y[16 * (c0 + c)];
+          p2i[c] += h2 * y[16 * (c0 + c) + 1];
         }
       if (lc == 0) lgs += mpole[(size_t)leaf_box[l4_src[q]] * P].x;
     }
-    p2r[0] += log(h) * lgs;  // zero unless lc == 0 (output l = 0)
+    if (c0 == 0) p2r[0] += log(h) * lgs;  // zero unless lc == 0 (output l = 0)
   }
+  static_for<0, NC>([&](auto cc) __attribute__((always_inline)) {
+    constexpr int c = decltype(cc)::value;
+    if (SPLIT && c != c0) {
+      if (c < c0) {  // on to t^(8c), the same product sequence as below
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
+        for (int i = 0; i < 8; ++i) tl = cmul(tl, t);
+      }
+      return;
+    }
     __syncthreads();
     // the eight outputs of the chunk accumulate side by side (k outer), so
     // their FMA chains interleave
@@ -591,9 +611,9 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
     const int l = 8 * c + lc;
     if (own && l < P) {
       const double2 sv = seg_sum(s_o + lc * kSoStride, r0, r1);
-      local[(size_t)bb * P + l] = make_double2(sv.x + p2r[c], sv.y + p2i[c]);
+      local[(size_t)bb * P + l] = make_double2(sv.x + p2r[SPLIT ? 0 : c], sv.y + p2i[SPLIT ? 0 : c]);
     }
-  }
+  });
 }
 
 // -------------------------------------------------------------------------
@@ -620,16 +640,6 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
 // (blockIdx % 8 == x) walk one contiguous range of work items; consecutive
 // items share a configuration and hence a table, which that XCD's L2 then
 // serves to all of them.
-// calls f(integral_constant<int, I>) for I = I0 .. N-1 (ring indices in an
-// unrolled pipeline stay compile-time constants)
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 template <int KD, int MTB>
 __global__ void __launch_bounds__(256) k_tgemm(int nitems, int MT, const int* __restrict__ t_cfg,
                                                const int* __restrict__ t_first, const int* __restrict__ t_count,
@@ -1767,6 +1777,8 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
 // leaves in a graph 918 and 979 us, 2510 leaves 159 and 129 us, 3808 leaves
 // 100 and 101 us, 4207 leaves 155 and 145 us)
 constexpr long kTwoStreamLeaves = 1000;
+// list-2 groups up to which M2L runs one work-group per chunk of outputs
+constexpr long kM2LSplitGroups = 512;
 
 int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut, double* fe, double* V,
                    hipStream_t s, std::string& err) {
@@ -1971,13 +1983,19 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   if (H.nlev > 2) {
     if (!one) VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
     const int ng = (int)H.m2l_grp.size() - 1;
+    const bool split = (long)ng * nrhs <= kM2LSplitGroups;
     if (ng > 0) {
 #define VFX_M2L(PMV)                                                                                             \
   hipLaunchKernelGGL(k_m2l_pairs<PMV>, dim3(ng, R), dim3(64), 0, s, P, T.root_size, D.m2l_grp, D.box_level,      \
                      D.l2_ptr, D.l2_src, D.l2_off, D.l2_tgt, D.l4_ptr, D.l4_src, D.l4_slot, D.leaf_box, T.p2l_rows, \
                      DT.pas_m2l_t, DT.m2l_logd, D.mpole, D.p2l_y, D.local, sMP, sPL)
 #define VFX_M2LL(PV)                                                                                             \
-  hipLaunchKernelGGL(k_m2l_lanes<PV>, dim3(ng, R), dim3(64), 0, s, T.root_size, D.m2l_grp, D.box_level,          \
+  if (split)                                                                                                     \
+    VFX_M2LS(PV, true, (PV + 7) / 8);                                                                            \
+  else                                                                                                           \
+    VFX_M2LS(PV, false, 1)
+#define VFX_M2LS(PV, SP, NZ)                                                                                     \
+  hipLaunchKernelGGL((k_m2l_lanes<PV, SP>), dim3(ng, R, NZ), dim3(64), 0, s, T.root_size, D.m2l_grp, D.box_level, \
                      D.l2_ptr, D.l2_src, D.l2_off, D.l2_tgt, D.l4_ptr, D.l4_src, D.l4_slot, D.leaf_box, T.p2l_rows, \
                      DT.pas_m2l_t, DT.m2l_logd, D.mpole, D.p2l_y, D.local, sMP, sPL)
       if (P == 21)
@@ -1994,6 +2012,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
         VFX_M2L(64);
 #undef VFX_M2L
 #undef VFX_M2LL
+#undef VFX_M2LS
     }
   }
   VFX_HIP(hipGetLastError());
