@@ -27,14 +27,15 @@ inline uint64_t key(int l, int x, int y) {
   return ((uint64_t)l << 58) | ((uint64_t)(uint32_t)x << 29) | (uint64_t)(uint32_t)y;
 }
 
-inline uint64_t morton(uint32_t x, uint32_t y) {
-  uint64_t r = 0;
-  for (int b = 0; b < 30; ++b) {
-    r |= (uint64_t)((x >> b) & 1u) << (2 * b);
-    r |= (uint64_t)((y >> b) & 1u) << (2 * b + 1);
-  }
-  return r;
+// bits of x at the even places, y at the odd ones (28 levels at most: 56 bits)
+inline uint64_t spread(uint64_t v) {
+  v = (v | (v << 16)) & 0x0000ffff0000ffffull;
+  v = (v | (v << 8)) & 0x00ff00ff00ff00ffull;
+  v = (v | (v << 4)) & 0x0f0f0f0f0f0f0f0full;
+  v = (v | (v << 2)) & 0x3333333333333333ull;
+  return (v | (v << 1)) & 0x5555555555555555ull;
 }
+inline uint64_t morton(uint32_t x, uint32_t y) { return spread(x) | (spread(y) << 1); }
 
 struct Node {
   int l, x, y, leaf;
@@ -258,12 +259,12 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
     return VFX_ETREE;
   }
   // order: level-major, Morton within a level
+  std::vector<std::pair<uint64_t, int>> keyed(nodes.size());
+  for (size_t i = 0; i < nodes.size(); ++i)
+    keyed[i] = {((uint64_t)nodes[i].l << 58) | morton(nodes[i].x, nodes[i].y), (int)i};
+  std::sort(keyed.begin(), keyed.end());
   std::vector<int> order(nodes.size());
-  for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-  std::sort(order.begin(), order.end(), [&](int a, int b) {
-    if (nodes[a].l != nodes[b].l) return nodes[a].l < nodes[b].l;
-    return morton(nodes[a].x, nodes[a].y) < morton(nodes[b].x, nodes[b].y);
-  });
+  for (size_t i = 0; i < order.size(); ++i) order[i] = keyed[i].second;
   const int B = (int)nodes.size();
   H.B = B;
   H.nlev = lmax + 1;
@@ -293,26 +294,52 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
     if (nd.leaf >= 0) H.leaf_box[nd.leaf] = i;
   }
   for (int l = 0; l < H.nlev; ++l) H.level_start[l + 1] += H.level_start[l];
-  auto find = [&](int l, int x, int y) -> int {
-    if (l < 0 || x < 0 || y < 0 || x >= (1 << l) || y >= (1 << l)) return -1;
-    auto it = idx.find(key(l, x, y));
-    return it == idx.end() ? -1 : it->second;
-  };
   for (int i = 0; i < B; ++i) {
-    const int l = H.box_level[i];
-    if (l > 0) H.box_parent[i] = find(l - 1, H.box_ix[i] >> 1, H.box_iy[i] >> 1);
-    if (H.box_leaf[i] < 0) H.box_child0[i] = find(l + 1, 2 * H.box_ix[i], 2 * H.box_iy[i]);
+    if (H.box_leaf[i] >= 0) continue;
+    H.box_child0[i] = idx.find(key(H.box_level[i] + 1, 2 * H.box_ix[i], 2 * H.box_iy[i]))->second;
+    // all four exist; in the Morton order they are consecutive (checked below)
+    for (int c = 0; c < 4; ++c)
+      if (H.box_child0[i] + c < B) H.box_parent[H.box_child0[i] + c] = i;
   }
   // children of a box are contiguous in the Morton order of the next level
   for (int i = 0; i < B; ++i)
     if (H.box_child0[i] >= 0)
       for (int c = 0; c < 4; ++c) {
         const int ch = H.box_child0[i] + c;
-        if (ch >= B || H.box_parent[ch] != i) {
+        if (ch >= B || H.box_level[ch] != H.box_level[i] + 1 || H.box_ix[ch] >> 1 != H.box_ix[i] ||
+            H.box_iy[ch] >> 1 != H.box_iy[i]) {
           err = "internal: children not contiguous";
           return VFX_EINVAL;
         }
       }
+  // colleagues: the boxes of the same level at offsets (dx, dy), |dx|, |dy| <=
+  // 1 (-1 for none), from the parents' (levels ascend in the box order, and a
+  // child's place in its parent is its Morton rank x + 2 y).  Every list is
+  // read off this table; looking each box up by its key took most of the
+  // plan's time.
+  std::vector<int> nbr((size_t)9 * B, -1);
+  auto col = [&](int b, int dx, int dy) { return nbr[(size_t)9 * b + 3 * (dx + 1) + dy + 1]; };
+  for (int b = 0; b < B; ++b) {
+    const int p = H.box_parent[b];
+    if (p < 0) {
+      nbr[(size_t)9 * b + 4] = b;
+      continue;
+    }
+    for (int dx = -1; dx <= 1; ++dx)
+      for (int dy = -1; dy <= 1; ++dy) {
+        const int x = (H.box_ix[b] & 1) + dx, y = (H.box_iy[b] & 1) + dy;  // in child units of the parent
+        const int q = col(p, x < 0 ? -1 : x >> 1, y < 0 ? -1 : y >> 1);
+        if (q >= 0 && H.box_child0[q] >= 0)
+          nbr[(size_t)9 * b + 3 * (dx + 1) + dy + 1] = H.box_child0[q] + (x & 1) + 2 * (y & 1);
+      }
+  }
+  // the parent's colleague that holds the position (x + dx, y + dy) of b's level
+  auto coarse = [&](int b, int dx, int dy) -> int {
+    const int p = H.box_parent[b];
+    if (p < 0) return -1;
+    const int x = (H.box_ix[b] & 1) + dx, y = (H.box_iy[b] & 1) + dy;
+    return col(p, x < 0 ? -1 : x >> 1, y < 0 ? -1 : y >> 1);
+  };
   H.kind.assign(tree->kind, tree->kind + L);
 
   // ---- extension lists ---------------------------------------------------
@@ -338,7 +365,7 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
         if (dx == 0 && dy == 0) continue;
         const int cx = x + dx, cy = y + dy;
         if (cx < 0 || cy < 0 || cx >= (1 << l) || cy >= (1 << l)) continue;
-        const int c = find(l, cx, cy);
+        const int c = col(b, dx, dy);
         if (c >= 0) {
           stack.assign(1, c);
           while (!stack.empty()) {
@@ -350,7 +377,7 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
               for (int q = 0; q < 4; ++q) stack.push_back(H.box_child0[u] + q);
           }
         } else {
-          const int p = find(l - 1, cx >> 1, cy >> 1);
+          const int p = coarse(b, dx, dy);
           if (p >= 0 && H.box_leaf[p] >= 0) cand.push_back(H.box_leaf[p]);
         }
       }
@@ -430,7 +457,7 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
       for (int dy = -1; dy <= 1; ++dy) {
         const int cx = x + dx, cy = y + dy;
         if (cx < 0 || cy < 0 || cx >= (1 << l) || cy >= (1 << l)) continue;
-        const int c = find(l, cx, cy);
+        const int c = col(b, dx, dy);
         if (c >= 0) {
           if (H.box_leaf[c] >= 0) {
             if (!zero_leaf[H.box_leaf[c]]) l1[leaf].push_back({H.box_leaf[c], (dx + 1) * 3 + (dy + 1)});
@@ -458,7 +485,7 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
             }
           }
         } else {
-          const int p = find(l - 1, cx >> 1, cy >> 1);
+          const int p = coarse(b, dx, dy);
           if (p < 0 || H.box_leaf[p] < 0) {
             err = "tree: not level-restricted (leaf " + std::to_string(leaf) +
                   " touches a leaf two levels coarser)";
@@ -511,7 +538,7 @@ int build_host_plan(const Tables& T, const vfx_tree* tree, HostPlan& H, std::str
       const int px = x >> 1, py = y >> 1;
       for (int dx = -1; dx <= 1; ++dx)
         for (int dy = -1; dy <= 1; ++dy) {
-          const int c = find(l - 1, px + dx, py + dy);
+          const int c = col(H.box_parent[b], dx, dy);
           if (c < 0) continue;
           if (H.box_leaf[c] < 0) {
             for (int q = 0; q < 4; ++q) {
