@@ -29,45 +29,81 @@ __device__ __forceinline__ xb_d4 xb_mfma(double a, double b, xb_d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// A1: work-group (cut leaf c, block of 64 right-hand sides); wave w takes the
-// 16 right-hand sides 64 blockIdx.y + 16 w + (0..15) and all NRT row tiles of
-// P_i.  A operand: F_I^T (right-hand side x interior index: the gathered
-// samples), B operand: P_i^T (interior index x row).  fg[(c nrhs + r) nG + row].
-template <int NRT>
+// A1: work-group (cut leaf c, block of 64 right-hand sides), all NRT row
+// tiles of P_i.  A operand: F_I^T (right-hand side x interior index: the
+// gathered samples), B operand: P_i^T (interior index x row); both are staged
+// in LDS 32 interior points at a time, one chunk ahead in registers, whole
+// rows of a chunk per load (read straight into the MFMA's lanes every load
+// touched 64 cache lines: 270 us for 32 right-hand sides of 730 cut leaves).
+// The block's 16-row groups of right-hand sides (NGRP = 1, 2 or 4) and the
+// row tiles are dealt to the four waves.  LDS rows 34 doubles apart: the 32
+// lanes of a half-wave read 32 different pairs of banks.
+// fg[(c nrhs + r) nG + row].
+constexpr int kA1K = 32, kA1LD = kA1K + 2;
+
+template <int NRT, int NGRP>
 __global__ void __launch_bounds__(256) k_ext_a1(int nG, int nX, const int* __restrict__ pinv_ptr,
                                                 const uint16_t* __restrict__ pinv_idx,
                                                 const double* __restrict__ pinv_val, const double* __restrict__ f_cut,
                                                 long sfc, int nrhs, double* __restrict__ fg) {
-  const int c = blockIdx.x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+  constexpr int WPG = 4 / NGRP, NT = (NRT + WPG - 1) / WPG;  // waves per group, row tiles per wave
+  constexpr int NF = 16 * NGRP * kA1K / 256, NP = 16 * NRT * kA1K / 256;
+  __shared__ double sF[16 * NGRP * kA1LD], sP[16 * NRT * kA1LD];
+  const int c = blockIdx.x, r0 = 64 * blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, lk = lane >> 4;
   const int off = pinv_ptr[c], ni = pinv_ptr[c + 1] - off;
-  const int r_a = 64 * blockIdx.y + 16 * w + li;  // this lane's A row (right-hand side)
-  const bool ok_a = r_a < nrhs;
-  const double* fc = f_cut + (size_t)(ok_a ? r_a : 0) * sfc + (size_t)c * nX;
   const double* P = pinv_val + (size_t)off * nG;
   const uint16_t* ix = pinv_idx + off;
-  xb_d4 acc[NRT];
+  const int kk = tid & (kA1K - 1), row = tid / kA1K;  // this thread's point of a chunk, first row
+  double rf[NF], rp[NP];
+  auto load = [&](int k0) {
+    const int k = k0 + kk;
+    const bool ok = k < ni;
+    const double* fc = f_cut + (size_t)c * nX + (ok ? ix[k] : 0);
 #pragma unroll
-  for (int t = 0; t < NRT; ++t) acc[t] = xb_d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int k = 0; k < ni; k += 4) {
-    const int kq = k + lk;
-    const bool ok = kq < ni;
-    const double a = (ok && ok_a) ? fc[ix[kq]] : 0.0;
+    for (int e = 0; e < NF; ++e) {
+      const int r = r0 + row + 8 * e;
+      rf[e] = ok && r < nrhs ? fc[(size_t)r * sfc] : 0.0;
+    }
 #pragma unroll
-    for (int t = 0; t < NRT; ++t) {
-      const int row = 16 * t + li;
-      const double b = (ok && row < nG) ? P[(size_t)row * ni + kq] : 0.0;
-      acc[t] = xb_mfma(a, b, acc[t]);
+    for (int e = 0; e < NP; ++e) {
+      const int g = row + 8 * e;
+      rp[e] = ok && g < nG ? P[(size_t)g * ni + k] : 0.0;
+    }
+  };
+  const int grp = w % NGRP, t0 = w / NGRP;
+  xb_d4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = xb_d4{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  for (int k0 = 0; k0 < ni; k0 += kA1K) {
+    __syncthreads();  // the previous chunk is read
+#pragma unroll
+    for (int e = 0; e < NF; ++e) sF[(row + 8 * e) * kA1LD + kk] = rf[e];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) sP[(row + 8 * e) * kA1LD + kk] = rp[e];
+    __syncthreads();
+    if (k0 + kA1K < ni) load(k0 + kA1K);
+    const int steps = min(kA1K, ni - k0 + 3) / 4;  // zero past the last interior point
+#pragma unroll
+    for (int s = 0; s < kA1K / 4; ++s) {
+      if (s >= steps) break;
+      const double a = sF[(16 * grp + li) * kA1LD + 4 * s + lk];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int rt = min(t0 + WPG * t, NRT - 1);
+        acc[t] = xb_mfma(a, sP[(16 * rt + li) * kA1LD + 4 * s + lk], acc[t]);
+      }
     }
   }
 #pragma unroll
-  for (int t = 0; t < NRT; ++t) {
-    const int row = 16 * t + li;
+  for (int t = 0; t < NT; ++t) {
+    const int rt = t0 + WPG * t, g = 16 * rt + li;
+    if (rt >= NRT) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int rhs = 64 * blockIdx.y + 16 * w + lk + 4 * r;
-      if (rhs < nrhs && row < nG) fg[((size_t)c * nrhs + rhs) * nG + row] = acc[t][r];
+      const int rhs = r0 + 16 * grp + lk + 4 * r;
+      if (rhs < nrhs && g < nG) fg[((size_t)c * nrhs + rhs) * nG + g] = acc[t][r];
     }
   }
 }
@@ -115,16 +151,21 @@ __global__ void __launch_bounds__(256) k_ext_a2(int nG, int Kb2, long cols, cons
 // Chebyshev coefficients c = C g C^T (total order < Kbar) and their values
 // at the K x K nodes of every target leaf of the cut leaf.  The target
 // geometry, C and the node positions are shared by the RB right-hand sides.
+// KT, KBT: compile-time K and Kbar (0: as passed); with run-time sizes the
+// index divisions cost more than the sums (197 us for 32 right-hand sides of
+// 730 cut leaves).
 constexpr int kEvalRB = 8;
 constexpr int kEvalMaxK = 16, kEvalMaxKb2 = 256;
 
-__global__ void __launch_bounds__(256) k_ext_eval(int K, int Kb, int nX, const int* __restrict__ ext_ptr,
+template <int KT, int KBT>
+__global__ void __launch_bounds__(256) k_ext_eval(int K_, int Kb_, int nX, const int* __restrict__ ext_ptr,
                                                   const int* __restrict__ ext_tgt, const double* __restrict__ ext_geo,
                                                   const double* __restrict__ t, const double* __restrict__ cbar,
                                                   const uint8_t* __restrict__ sbar_given,
                                                   const double* __restrict__ f_cut, long sfc,
                                                   const double* __restrict__ g_pre, double* __restrict__ fe, long sfe,
                                                   int nrhs) {
+  const int K = KT ? KT : K_, Kb = KBT ? KBT : Kb_;
   __shared__ double s_cb[kEvalMaxKb2];
   __shared__ double s_g[kEvalRB * kEvalMaxKb2];
   __shared__ double s_tmp[kEvalRB * kEvalMaxKb2];  // C g, then the evaluation's partial products
@@ -209,9 +250,21 @@ int launch_ext_eval(const Plan* p, const double* f_cut, double* fe, int nrhs, hi
     return VFX_EINVAL;
   }
   const long sfc = (long)H.ncut * T.nX, sfe = (long)H.L * T.n;
-  hipLaunchKernelGGL(k_ext_eval, dim3(H.ncut, (nrhs + kEvalRB - 1) / kEvalRB), dim3(256), 0, s, T.K, T.Kbar, T.nX,
-                     D.ext_ptr, D.ext_tgt, D.ext_geo, p->ctx->D.t, p->ctx->D.cbar, D.sbar_given, f_cut, sfc,
-                     D.ext_g, fe, sfe, nrhs);
+#define VFX_EVAL(KV, KBV)                                                                                          \
+  hipLaunchKernelGGL((k_ext_eval<KV, KBV>), dim3(H.ncut, (nrhs + kEvalRB - 1) / kEvalRB), dim3(256), 0, s, T.K,    \
+                     T.Kbar, T.nX, D.ext_ptr, D.ext_tgt, D.ext_geo, p->ctx->D.t, p->ctx->D.cbar, D.sbar_given, f_cut, \
+                     sfc, D.ext_g, fe, sfe, nrhs)
+  if (T.Kbar != 12)
+    VFX_EVAL(0, 0);
+  else if (T.K == 16)
+    VFX_EVAL(16, 12);
+  else if (T.K == 12)
+    VFX_EVAL(12, 12);
+  else if (T.K == 8)
+    VFX_EVAL(8, 12);
+  else
+    VFX_EVAL(4, 12);
+#undef VFX_EVAL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     err = std::string("batched extension: ") + hipGetErrorString(e);
@@ -237,15 +290,23 @@ int launch_ext_gemm(const Plan* p, const double* f_cut, int nrhs, hipStream_t s,
     return VFX_EINVAL;
   }
   const dim3 g1(H.ncut, (nrhs + 63) / 64);
-#define VFX_A1(N)                                                                                                   \
-  case N:                                                                                                           \
-    hipLaunchKernelGGL(k_ext_a1<N>, g1, dim3(256), 0, s, nG, T.nX, D.pinv_ptr, D.pinv_idx, D.pinv_val, f_cut, sfc, \
-                       nrhs, D.ext_fg);                                                                             \
+#define VFX_A1G(N, G)                                                                                               \
+  hipLaunchKernelGGL((k_ext_a1<N, G>), g1, dim3(256), 0, s, nG, T.nX, D.pinv_ptr, D.pinv_idx, D.pinv_val, f_cut,    \
+                     sfc, nrhs, D.ext_fg)
+#define VFX_A1(N)      \
+  case N:              \
+    if (nrhs <= 16)    \
+      VFX_A1G(N, 1);   \
+    else if (nrhs <= 32) \
+      VFX_A1G(N, 2);   \
+    else               \
+      VFX_A1G(N, 4);   \
     break;
   switch (nrt) {
     VFX_A1(1) VFX_A1(2) VFX_A1(3) VFX_A1(4) VFX_A1(5) VFX_A1(6) VFX_A1(7) VFX_A1(8) VFX_A1(9)
   }
 #undef VFX_A1
+#undef VFX_A1G
   const long cols = (long)H.ncut * nrhs;
   const dim3 g2((unsigned)((cols + 63) / 64));
   const DeviceTables& DT = p->ctx->D;
