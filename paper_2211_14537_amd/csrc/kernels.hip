@@ -89,14 +89,18 @@ __device__ __forceinline__ void fe_init_range(long e0, long e1, long step, int n
   }
 }
 
-template <int NT>
+// KT, KBT: compile-time K and Kbar (0: as passed): the index divisions of the
+// evaluation by run-time sizes cost a 64-leaf tree 2 us of 45, 2510 leaves
+// 4 us of 139
+template <int NT, int KT, int KBT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 ? 6 : 4))) k_extension(
-    int K, int Kb, int nX, int nG, const int* __restrict__ pinv_ptr, const uint16_t* __restrict__ pinv_idx,
+    int K_, int Kb_, int nX, int nG, const int* __restrict__ pinv_ptr, const uint16_t* __restrict__ pinv_idx,
     const double* __restrict__ pinv_val, const uint8_t* __restrict__ sbar_given, const int* __restrict__ ext_ptr,
     const int* __restrict__ ext_tgt, const double* __restrict__ ext_geo, const double* __restrict__ t,
     const double* __restrict__ AbarT, const double* __restrict__ cbar, const double* __restrict__ f_cut,
     double* __restrict__ fe, int nrhs, long sfc, long sfe, int ext_blocks, int L,
     const int8_t* __restrict__ fe_src, const double* __restrict__ f_leaf) {
+  const int K = KT ? KT : K_, Kb = KBT ? KBT : Kb_;
   const long half = (long)L * K * K / 2, pieces = half * nrhs;
   if ((int)blockIdx.x >= ext_blocks) {
     // the work-groups past the cut leaves initialise f^e of the other
@@ -1864,17 +1868,30 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     const int blocks1 = gemm ? 0 : ext_blocks;
     const int nt = blocks1 > 0 && blocks1 <= kExtOnePerCu ? 1024 : blocks1 > 0 && blocks1 <= 2 * kExtOnePerCu ? 512 : 256;
     const int copy_blocks = (int)std::min<long>((pieces + nt - 1) / nt, 262144 / nt);
-#define VFX_EXT(NTV)                                                                                               \
-  hipLaunchKernelGGL(k_extension<NTV>, dim3(blocks1 + copy_blocks), dim3(NTV), 0, s, T.K, T.Kbar, T.nX, T.nG,      \
+#define VFX_EXT(NTV)                \
+  if (T.Kbar != 12)                 \
+    VFX_EXTK(NTV, 0, 0);            \
+  else if (T.K == 16)               \
+    VFX_EXTK(NTV, 16, 12);          \
+  else if (T.K == 12)               \
+    VFX_EXTK(NTV, 12, 12);          \
+  else if (T.K == 8)                \
+    VFX_EXTK(NTV, 8, 12);           \
+  else                              \
+    VFX_EXTK(NTV, 4, 12)
+#define VFX_EXTK(NTV, KV, KBV)                                                                                     \
+  hipLaunchKernelGGL((k_extension<NTV, KV, KBV>), dim3(blocks1 + copy_blocks), dim3(NTV), 0, s, T.K, T.Kbar, T.nX, T.nG,      \
                      D.pinv_ptr, D.pinv_idx, D.pinv_val, D.sbar_given, D.ext_ptr, D.ext_tgt, D.ext_geo, DT.t,      \
                      DT.AbarT, DT.cbar, f_cut, fe, nrhs, sFC, sFL, blocks1, L, D.fe_src, f_leaf)
-    if (nt == 1024)
+    if (nt == 1024) {
       VFX_EXT(1024);
-    else if (nt == 512)
+    } else if (nt == 512) {
       VFX_EXT(512);
-    else
+    } else {
       VFX_EXT(256);
+    }
 #undef VFX_EXT
+#undef VFX_EXTK
   }
   VFX_HIP(hipGetLastError());
   MARK(1, s);
