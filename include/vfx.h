@@ -252,17 +252,19 @@ int vfx_net_charge_noalloc_max_rhs(void);
 int vfx_plan_set_precision(vfx_plan* plan, int mode, int min_level);
 
 /* Near-field strategy of the FP64 path at K = 16.  mode 0 (the default):
- * pair-based - every list-1 pair's table product is formed on its own
- * (configuration-major tiles of 32-64 pairs, operators shared through LDS)
- * and the far-field kernel sums each target's pair products.  mode 1:
+ * from
+ * exterior moments - a leaf acts outside itself only through 4 (2K-4)
+ * moments of its data, reflected neighbours share their operators, and a
+ * target's same-level sources are summed in registers; pairs across levels
+ * leave one row each, which the far-field kernel sums.  mode 1:
  * target-stationary - the products of each group of 16 consecutive target
  * leaves are summed in registers and each leaf's near-field sum is written
  * once: the 32 neighbour configurations are folded onto six symmetry
  * classes of the square (T_c = P_g T_b P_g^T, Section 4 tables in
  * low-rank form Q_b W_b), a table GEMM forms every pair's W_b P_g^T f, and a
  * per-group kernel applies Q_b and the self table.  Both compute the same
- * sum (they differ by rounding); mode 1 reads and writes far less memory
- * but does more matrix work (tiles of one pair per target).  Other K and
+ * sum (they differ by rounding); mode 1 does about three times the matrix
+ * work.  Other K and
  * mixed pairs keep mode 0.  The plan's device data are rebuilt on the next
  * vfx_execute (graphs that captured it are invalidated); the call must not
  * overlap an execute of the same plan.  VFX_EINVAL for other modes. */
@@ -307,8 +309,8 @@ int vfx_execute_batch(vfx_plan* plan, int nrhs, const double* f_leaf, const doub
 
 /* Launch-parameter autotuner: times `reps` executes of the given batch
  * for each candidate (work-group cap of the persistent near-field kernels
- * 256/512/768/1024; row tiles per block of the dense near-field GEMM 4/8 at
- * K = 16) with HIP events on `stream` and keeps the fastest for later
+ * 256/512/768/1024; dense_mtb 4/8 at
+ * K = 16, which changes nothing at present) with HIP events on `stream` and keeps the fastest for later
  * executes of the plan; choice[0..1] (optional) receive it.  The choices
  * change only how work is distributed, not the arithmetic: results are
  * bitwise independent of them.  The buffers are overwritten. */
@@ -318,8 +320,8 @@ int vfx_plan_autotune(vfx_plan* plan, int nrhs, const double* f_leaf, const doub
 /* Set the same two launch parameters directly (for example the choice an
  * earlier autotune made): the work-group cap of the persistent near-field
  * kernels (1..65535; default 512, two work-groups per CU; the int8 near
- * field of precision mode 2 takes three quarters of it) and the row
- * tiles per block of the dense near-field GEMM (4 or 8).  Results are
+ * field of precision mode 2 takes three quarters of it) and dense_mtb (4 or
+ * 8), which no present kernel depends on.  Results are
  * bitwise independent of them.  VFX_EINVAL outside those ranges. */
 int vfx_plan_set_launch(vfx_plan* plan, int near_wgs, int dense_mtb);
 
@@ -359,15 +361,17 @@ int vfx_graph_destroy(vfx_graph* graph);
  * milliseconds of eleven phases:
  *   ms[0] extension (the cut-leaf kernel, with the f^e initialisation of
  *         the other leaves)
- *   ms[1] P2M and the upward pass
- *   ms[2] M2L (with the wait for P2L)
+ *   ms[1] exterior moments, P2M and the upward pass
+ *   ms[2] M2L (with the wait for P2L, or with P2L itself if pairs are in
+ *         mixed precision)
  *   ms[3] downward pass (leaf local expansions)
- *   ms[4] near field, first kernel (side stream): the low-rank pairs, or on
+ *   ms[4] near field, first kernel (side stream): the FP64 pairs, or on
  *         the target-stationary path (FP64, K = 16) the factor products
- *   ms[5] near field, second kernel (side stream): the dense pairs, or the
- *         per-target-group kernel of the target-stationary path
+ *   ms[5] near field, second kernel (side stream): the pairs in mixed
+ *         precision, or the per-target-group kernel of the target-stationary
+ *         path
  *   ms[6] far field (list-1 and list-3 sums, L2P)   ms[7] total
- *   ms[8] P2L, list-4 products (side stream)
+ *   ms[8] P2L, list-4 products (side stream; 0 with pairs in mixed precision)
  *   ms[9] M2P, list-3 products (side stream, after the near field and the
  *         upward pass)
  *   ms[10] f^e initialisation: 0 (it runs inside the extension launch,
@@ -424,6 +428,9 @@ int vfx_plan_timings(vfx_plan* plan, double* ms, int n_out);
  *            exponents, Q slices [s][i][a], n Q exponents (64 ranks,
  *            padded); 26, 28 (`index` ignored): the self table's slices
  *            [s][i][j] and its n row exponents
+ *        29..32 (`index` ignored): the FP64 near field's operands - exterior
+ *            moments of the leaf basis, moments and P2M as one operand, the
+ *            same-level operators and the cross-level operators per parity
  * VFX_EINVAL if `which`, `index` or `count` does not match. */
 int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64_t count);
 /* Interaction list `which` (1..4) of a plan as CSR arrays (host):

@@ -690,15 +690,25 @@ int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64
       size = (int64_t)v[which - 29]->size();
       break;
     }
+    case 19: {  // table 3 as a real operand, [j][2l, 2l + 1], rows padded
+      static thread_local std::vector<double> v;
+      const size_t R = T.p2l_rows, P = T.p + 1;
+      v.assign((size_t)vfx::kP2LSlots * n * R, 0.0);
+      for (size_t sl = 0; sl < (size_t)vfx::kP2LSlots * P; ++sl)
+        for (size_t j = 0; j < (size_t)n; ++j)
+          for (int c = 0; c < 2; ++c) v[(sl / P * n + j) * R + 2 * (sl % P) + c] = T.p2l[2 * (sl * n + j) + c];
+      src = v.data();
+      size = (int64_t)v.size();
+      break;
+    }
     case 23:
       if (index < 0 || index >= vfx::kP2LSlots) break;
       src = T.m2p_gemm.data() + (size_t)index * T.p2l_rows * n;
       size = (int64_t)T.p2l_rows * n;
       break;
-    case 9: case 10: case 11: case 12: case 13: case 14: case 15: case 16: case 17: case 18: case 19: {
+    case 9: case 10: case 11: case 12: case 13: case 14: case 15: case 16: case 17: case 18: {
       const std::vector<double>* v[] = {&T.pas_m2l, &T.m2l_tpow, &T.m2l_tneg, &T.m2l_logd, &T.pas_m2m,
-                                        &T.m2m_in,  &T.m2m_out,  &T.pas_l2l,  &T.l2l_in,   &T.l2l_out,
-                                        &T.p2l_gemm};
+                                        &T.m2m_in,  &T.m2m_out,  &T.pas_l2l,  &T.l2l_in,   &T.l2l_out};
       src = v[which - 9]->data();
       size = (int64_t)v[which - 9]->size();
       break;

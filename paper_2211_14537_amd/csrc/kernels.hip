@@ -1,17 +1,21 @@
 // Device side of the extension + volume FMM path (gfx950, FP64).
 //
-// Execution order on one stream (every output element has one writer, so no
-// atomics are needed and results are bitwise reproducible):
+// Execution order (every output element has one writer, so no atomics are
+// needed and results are bitwise reproducible); on the caller's stream, with
+// P2L, the near field and M2P on a second one for all but small trees:
 //   extension    f^e = f on regular leaves, 0 on leaves outside every
 //                extension list, and per cut leaf: f_G = P_i f_{X^I}; values on the Kbar grid of
 //                Sbar (given data where interior); total-order Chebyshev
 //                expansion; evaluation on every leaf of its extension list
 //                (Sections 3.2 and 4.1)
-//   p2m, m2m     multipole expansions, leaves then upward
-//   m2l          local expansions from list 2 (M2L) and list 4 (P2L)
-//   l2l          locals downward
-//   near         list 1 by the precomputed tables
-//   far          L2P of the local expansion and M2P of list 3
+//   moments      exterior moments and multipoles of the leaves (near_sym.hip)
+//   up           multipoles of the other boxes
+//   p2l, near    list 4 and list 1 from the moments (near_sym.hip), or list 1
+//                in mixed precision (mixed.hip, mixed8.hip)
+//   m2l          local expansions from list 2 and the list-4 products
+//   m2p          list 3
+//   down         full local expansions of the leaves
+//   far          L2P of the local expansion and the sums of lists 1 and 3
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -1781,7 +1785,10 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
 // leaves in a graph 918 and 979 us, 2510 leaves 159 and 129 us, 3808 leaves
 // 100 and 101 us, 4207 leaves 155 and 145 us)
 constexpr long kTwoStreamLeaves = 1000;
-// list-2 groups up to which M2L runs one work-group per chunk of outputs
+// list-2 groups up to which M2L runs one work-group per chunk of outputs: two
+// groups per CU, beyond which the chunks' repeated source loads cost more than
+// the idle CUs (64 leaves 48 -> 45 us, ten trees of up to a few hundred leaves
+// 824 -> 778 us; a limit of 2000 took 2510 leaves from 139 to 163 us)
 constexpr long kM2LSplitGroups = 512;
 
 int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut, double* fe, double* V,

@@ -375,9 +375,9 @@ int launch_near_f8(const Plan* p, int nrhs, int max_wgs, hipStream_t s, std::str
   const F8List dn{4 * (int)H.mt_cfg.size(), 4, D.mt_cfg, D.mt_first, D.mt_count, DT.f8_A, DT.f8_Aexp};
   const int items = lr.nitems + dn.nitems;
   // three quarters of the FP64 near-field kernels' work-group cap: this
-  // kernel runs beside M2L on the caller's stream and finishes early, so
-  // fewer resident work-groups leave M2L more room (wedge workload, int8
-  // mixed step: 0.340 ms at 384 work-groups against 0.352 ms at 512)
+  // kernel runs beside the upward pass and M2L on the caller's stream, and
+  // fewer resident work-groups leave those more room (14254 leaves, int8
+  // mixed step: 343 us at 512 work-groups, 323 at 384, 349 at 256)
   const int cap = max_wgs > 0 ? std::max(8, max_wgs * 3 / 4) : 0;
   if (items > 0)
     hipLaunchKernelGGL(k_near_f8<kF8Slices>, dim3(persistent_grid_f8(items, cap), nrhs), dim3(256), 0, s, lr, dn,

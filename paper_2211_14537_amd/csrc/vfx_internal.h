@@ -343,7 +343,10 @@ int launch_net_charge(Plan* p, const double* fe, int nrhs, double* out, hipStrea
 __host__ __device__ constexpr int moment_stride(int E) { return (E + 15) / 16 * 16; }
 // near_sym.hip: exterior moments and P2M; FP64 list 1; P2L.  At K = 16 a work
 // item holds 64 targets where that makes at least kSymItems4 items, 32 where
-// those make kSymItems2, else 16.
+// those make kSymItems2, else 16: an item reads its operators once for its
+// targets, but too few items leave CUs idle (16 or 32 targets everywhere:
+// 14254 leaves 277 and 280 us per execute against 273, a batch of 32 on 2510
+// leaves 2377 and 2339 against 2297).
 constexpr long kSymItems4 = 512, kSymItems2 = 256;
 int launch_moments(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err);
 int launch_near_sym(const Plan* p, const double* fe, int nrhs, int max_wgs, hipStream_t s, std::string& err);
