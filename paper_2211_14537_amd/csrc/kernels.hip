@@ -491,13 +491,21 @@ __global__ void __launch_bounds__(64) k_m2l_pairs(int P, double root_size, const
 // (compile-time loops, so the Pascal coefficients, read through wave-uniform
 // pointers, become scalar operands of the FMAs and need no LDS traffic).
 
+// complex product with its fused operations named: both forms of k_m2l_lanes
+// round alike, so a right-hand side of a batch keeps the bits of a single
+// execute whichever form each takes
+__device__ __forceinline__ double2 cmul_fma(double2 a, double2 b) {
+  return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.x, b.y, a.y * b.x));
+}
+
 // M2L: one lane per list-2 entry (target, source), for a group of
 // consecutive target boxes with at most 64 entries and at most 8 boxes.
 // Lane e holds s_k = (-t)^k a_k of its source; for each output l it forms
 // t^l sum_k C(k+l-1,l) s_k (minus a_0 t^l/l; plus a_0 (log|d/h| + log h) for
 // l = 0).  Per-target sums go through LDS in chunks of 8 outputs, in entry
-// order (deterministic), together with the P2L contributions.  SPLIT (small trees, whose groups leave SIMDs empty): one
-// work-group per chunk of outputs, each forming the s_k again.
+// order (deterministic), together with the P2L contributions.  SPLIT (small
+// trees, whose groups leave SIMDs empty): one work-group per chunk of outputs,
+// each forming the s_k again.
 template <int P, bool SPLIT>
 __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* __restrict__ grp,
                                                   const int* __restrict__ box_level, const int* __restrict__ l2_ptr,
@@ -530,8 +538,8 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
 #pragma unroll
     for (int k = 0; k < P; ++k) {
       const double2 a = act ? mpole[(size_t)src * P + k] : make_double2(0.0, 0.0);
-      s[k] = cmul(pw, a);
-      pw = cmul(pw, mt);
+      s[k] = cmul_fma(pw, a);
+      pw = cmul_fma(pw, mt);
     }
   }
   const double a0 = s[0].x;
@@ -564,19 +572,19 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
 #pragma unroll
       for (int c = 0; c < NP; ++c)
         if (8 * (c0 + c) + lc < P) {
-          p2r[c] += h2 * y[16 * (c0 + c)];
-          p2i[c] += h2 * y[16 * (c0 + c) + 1];
+          p2r[c] = __builtin_fma(h2, y[16 * (c0 + c)], p2r[c]);
+          p2i[c] = __builtin_fma(h2, y[16 * (c0 + c) + 1], p2i[c]);
         }
       if (lc == 0) lgs += mpole[(size_t)leaf_box[l4_src[q]] * P].x;
     }
-    if (c0 == 0) p2r[0] += log(h) * lgs;  // zero unless lc == 0 (output l = 0)
+    if (c0 == 0) p2r[0] = __builtin_fma(log(h), lgs, p2r[0]);  // zero unless lc == 0 (output l = 0)
   }
   static_for<0, NC>([&](auto cc) __attribute__((always_inline)) {
     constexpr int c = decltype(cc)::value;
     if (SPLIT && c != c0) {
       if (c < c0) {  // on to t^(8c), the same product sequence as below
 #pragma unroll
-        for (int i = 0; i < 8; ++i) tl = cmul(tl, t);
+        for (int i = 0; i < 8; ++i) tl = cmul_fma(tl, t);
       }
       return;
     }
@@ -593,8 +601,8 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
         const int l = 8 * c + lc;
         if (l < P) {
           const double cf = pasT[l * P + k];
-          ur[lc] += cf * s[k].x;
-          ui[lc] += cf * s[k].y;
+          ur[lc] = __builtin_fma(cf, s[k].x, ur[lc]);
+          ui[lc] = __builtin_fma(cf, s[k].y, ui[lc]);
         }
       }
     }
@@ -603,15 +611,15 @@ __global__ void __launch_bounds__(64) k_m2l_lanes(double root_size, const int* _
       const int l = 8 * c + lc;
       double2 out = make_double2(0.0, 0.0);
       if (l < P) {
-        out = cmul(tl, make_double2(ur[lc], ui[lc]));
+        out = cmul_fma(tl, make_double2(ur[lc], ui[lc]));
         if (l == 0) {
           out.x += lg0;
         } else {
           const double il = 1.0 / (double)l;  // compile-time constant
-          out.x -= a0 * tl.x * il;
-          out.y -= a0 * tl.y * il;
+          out.x = __builtin_fma(-(a0 * tl.x), il, out.x);
+          out.y = __builtin_fma(-(a0 * tl.y), il, out.y);
         }
-        tl = cmul(tl, t);
+        tl = cmul_fma(tl, t);
       }
       s_o[lc * kSoStride + lane] = act ? out : make_double2(0.0, 0.0);
     }

@@ -83,11 +83,13 @@ def test_column_heights(gpu_device, K, Kbar):
     assert w <= 1.0
 
 
-@pytest.mark.parametrize("nrhs", [2, 5, 6, 7])
-def test_work_group_sizes_bitwise(gpu_device, nrhs):
+@pytest.mark.parametrize("name,p,nrhs", [("starfish_small", 24, 2), ("starfish_small", 24, 5),
+                                         ("starfish_small", 20, 6), ("starfish_small", 24, 7),
+                                         ("disk_adaptive_small", 30, 3), ("disk_adaptive_small", 40, 3)])
+def test_work_group_sizes_bitwise(gpu_device, name, p, nrhs):
     import torch
-    G.say(f"case starfish_small nrhs={nrhs}")
-    case = G.setup("starfish_small", p=24)
+    G.say(f"case {name} p={p} nrhs={nrhs}")
+    case = G.setup(name, p=p)
     fl, fc = inputs(case, nrhs, 5)
     FE, V = batch(case, fl, fc, gpu_device)
     for r in (0, nrhs - 1):
