@@ -98,3 +98,27 @@ def test_work_group_sizes_bitwise(gpu_device, name, p, nrhs):
         case["plan"].execute(d, torch.tensor(fc[r], device=gpu_device), fe, v)
         torch.cuda.synchronize()
         assert torch.equal(FE[r], fe) and torch.equal(V[r], v)
+
+
+@pytest.mark.parametrize("nrhs", [2, 3])
+def test_extension_work_groups_bitwise(gpu_device, nrhs):
+    """182 cut leaves: 1024 threads for one right-hand side, 512 for two, 256
+    for three."""
+    import torch
+    cfg = get_config("starfish_small")
+    cfg["K"] = 4
+    ctx = vfx.Context(4, 20, root=cfg["root"])
+    tr = T.build_tree(cfg, ctx.stencil_points())
+    assert len(tr["cut_ids"]) <= 256 < 2 * len(tr["cut_ids"]) <= 512 < 3 * len(tr["cut_ids"])
+    fl, fc = T.sample_inputs(cfg, tr, ctx.stencil_points())
+    plan = vfx.Plan(ctx, tr["level"], tr["ix"], tr["iy"], tr["kind"], tr["mask"])
+    case = dict(f_leaf=fl, f_cut=fc, plan=plan)
+    G.say(f"case starfish_small K=4 nrhs={nrhs}")
+    fl, fc = inputs(case, nrhs, 6)
+    FE, V = batch(case, fl, fc, gpu_device)
+    for r in range(nrhs):
+        d = torch.tensor(fl[r], device=gpu_device)
+        fe, v = torch.empty_like(d), torch.empty_like(d)
+        plan.execute(d, torch.tensor(fc[r], device=gpu_device), fe, v)
+        torch.cuda.synchronize()
+        assert torch.equal(FE[r], fe) and torch.equal(V[r], v)
