@@ -173,8 +173,8 @@ struct SymArgs {
 //   A  the combined source values, 16-byte pieces of whole rows (224 or 256
 //      contiguous bytes), so that a load touches a dozen cache lines; read
 //      straight into the MFMA's lanes every load would touch 32 to 64, and
-//      that, not the matrix cores, bounded the kernel (14254 leaves: 93 us against 62,
-//      of which the matrix cores are busy 58%);
+//      that, not the matrix cores, bounded the kernel (14254 leaves: 93 us against 62;
+//      matrix cores busy 45% of it, 58% in a batch of 32);
 //   B  the table block, 28 or 32 rows of 64.
 // LDS rows: A 34 doubles (the 32 lanes of a half-wave read 32 different
 // pairs of banks), B 64 doubles with the tiles of odd lane groups swapped in
