@@ -1548,9 +1548,23 @@ void free_tables_device(Context* c) {
   D = DeviceTables();
 }
 
-// Buffers that hold one copy per right-hand side (expansions, near-field
-// partials, P2L partials, leaf local expansions, bf16 slices): reallocated
-// for `nrhs` copies when a larger batch is requested.
+// Buffers that hold one copy per right-hand side (expansions, moments,
+// near-field, P2L and M2P rows, leaf local expansions, slices, the batched
+// extension's products): this one list is what a larger batch reallocates and
+// what goes with the plan's device data.
+static void free_rhs_buffers(DevicePlan& D) {
+  void* bufs[] = {D.mpole, D.local, D.mom,  D.ysym,   D.near_y, D.near_z, D.p2l_y, D.m2p_y,
+                  D.up_part, D.locf, D.xs, D.xs_exp, D.ext_fg, D.ext_g};
+  for (void* q : bufs)
+    if (q) (void)hipFree(q);
+  D.mpole = D.local = D.up_part = D.locf = nullptr;
+  D.mom = D.ysym = D.near_y = D.near_z = D.p2l_y = D.m2p_y = nullptr;
+  D.xs = nullptr;
+  D.xs_exp = nullptr;
+  D.ext_fg = D.ext_g = nullptr;
+  D.cap = 0;
+}
+
 int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err) {
   const HostPlan& H = p->H;
   DevicePlan& D = p->D;
@@ -1558,17 +1572,7 @@ int ensure_rhs_capacity(Plan* p, int nrhs, std::string& err) {
   const size_t P = T.p + 1, R = (size_t)nrhs;
   if (D.cap > 0) (void)hipDeviceSynchronize();  // no execute of this plan in flight
   p->gen++;  // graphs that captured the old buffers are stale
-  void* old[] = {D.mpole, D.local, D.near_y, D.p2l_y, D.up_part, D.locf, D.xs, D.m2p_y, D.xs_exp, D.near_z,
-                 D.ext_fg, D.ext_g, D.mom, D.ysym};
-  for (void* q : old)
-    if (q) (void)hipFree(q);
-  D.mpole = D.local = D.up_part = D.locf = nullptr;
-  D.near_y = D.p2l_y = D.m2p_y = D.near_z = nullptr;
-  D.mom = D.ysym = nullptr;
-  D.xs = nullptr;
-  D.xs_exp = nullptr;
-  D.ext_fg = D.ext_g = nullptr;
-  D.cap = 0;
+  free_rhs_buffers(D);
   VFX_HIP(hipMalloc((void**)&D.mpole, sizeof(double2) * (size_t)H.B * P * R));
   VFX_HIP(hipMalloc((void**)&D.local, sizeof(double2) * (size_t)H.B * P * R));
   VFX_HIP(hipMemset(D.local, 0, sizeof(double2) * (size_t)H.B * P * R));
@@ -1712,19 +1716,15 @@ void free_plan_device(Plan* p) {
   DevicePlan& D = p->D;
   if (D.ready) (void)hipDeviceSynchronize();  // no execute of this plan in flight
   p->gen++;
-  void* ptrs[] = {D.box_level, D.box_next, D.box_parent, D.box_cx,   D.box_cy,   D.leaf_box,
-                  D.kind,      D.l1_ptr,     D.l1_src,   D.l1_cfg,     D.l2_ptr,   D.l2_src,   D.l2_off,
-                  D.l3_ptr,    D.l3_src,     D.l4_ptr,   D.l4_src,     D.l4_cfg,   D.np_src,   D.y_ptr,
-                  D.y_slot,    D.sy_nb,      D.sy_row,   D.near_y,     D.p4_src,   D.l4_slot,  D.t4_cfg,
-                  D.t4_first,  D.t4_count,   D.p2l_y,    D.cut_leaf,   D.ext_ptr,  D.ext_tgt,  D.pinv_ptr,
-                  D.pinv_idx,  D.pinv_val,   D.sbar_given, D.mpole,    D.local,    D.mom,
-                  D.ysym,      D.leaf_ids,   D.l2_tgt,   D.m2l_grp,  D.up_box,   D.up_ptr,   D.up_src,
-                  D.up_pos,    D.up_split,   D.up_grp,   D.up_part,  D.anc_ptr,  D.anc,
-                  D.nl_cfg,    D.nl_first,   D.nl_count, D.l1_srcbox,  D.ext_geo,
-                  D.anc_leaf,  D.dn_grp,     D.locf,     D.mt_cfg,   D.mt_first, D.mt_count, D.ml_cfg, D.fac_ws,
-                  D.ml_first,  D.ml_count,   D.xs,       D.p3_src,   D.l3_slot,  D.t3_cfg,   D.t3_first,
-                  D.t3_count,  D.m2p_y,    D.xs_exp,   D.chg_part, D.near_z, D.ts_grp, D.ts_tcls,
-                  D.ts_row,    D.ts_code,  D.fe_src};
+  free_rhs_buffers(D);
+  void* ptrs[] = {D.box_level, D.box_next, D.box_parent, D.box_cx, D.box_cy, D.leaf_box, D.kind, D.l1_ptr, D.l1_src,
+                  D.l1_cfg, D.l2_ptr, D.l2_src, D.l2_off, D.l3_ptr, D.l3_src, D.l4_ptr, D.l4_src, D.l4_cfg, D.np_src,
+                  D.y_ptr, D.y_slot, D.sy_nb, D.sy_row, D.p4_src, D.l4_slot, D.t4_cfg, D.t4_first, D.t4_count,
+                  D.cut_leaf, D.ext_ptr, D.ext_tgt, D.pinv_ptr, D.pinv_idx, D.pinv_val, D.sbar_given, D.leaf_ids,
+                  D.l2_tgt, D.m2l_grp, D.up_box, D.up_ptr, D.up_src, D.up_pos, D.up_split, D.up_grp, D.anc_ptr, D.anc,
+                  D.nl_cfg, D.nl_first, D.nl_count, D.l1_srcbox, D.ext_geo, D.anc_leaf, D.dn_grp, D.mt_cfg,
+                  D.mt_first, D.mt_count, D.ml_cfg, D.fac_ws, D.ml_first, D.ml_count, D.p3_src, D.l3_slot, D.t3_cfg,
+                  D.t3_first, D.t3_count, D.chg_part, D.ts_grp, D.ts_tcls, D.ts_row, D.ts_code, D.fe_src};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   D = DevicePlan();
