@@ -1793,6 +1793,31 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
 // leaves in a graph 918 and 979 us, 2510 leaves 159 and 129 us, 3808 leaves
 // 100 and 101 us, 4207 leaves 155 and 145 us)
 constexpr long kTwoStreamLeaves = 1000;
+// The same with mixed pairs.  The bf16 kernel takes 45 us and more on the
+// smallest trees, so it is worth hiding behind M2L as soon as that is long:
+// from leaves times P^2 of 250000 on (one and two streams: p = 20, 256 leaves
+// 90 and 105 us, 808 leaves 125 and 118; p = 24, 256 leaves 92 and 110, 532
+// leaves 124 and 115; p = 30, 376 leaves 126 and 119; p = 40, 376 leaves 148
+// and 120), and for every tree whose order has no compile-time M2L (p = 27, 64
+// leaves 138 and 111 us, 976 leaves 196 and 163).  The int8 kernel is shorter:
+// as FP64, but for those orders from 400 leaves on (p = 17, 256 leaves 93 and
+// 101 us, 808 leaves 130 and 121; p = 27, 532 leaves 150 and 143).
+constexpr long kTwoStreamBf16Work = 250000, kTwoStreamInt8General = 400;
+// expansion lengths P with a compile-time M2L (k_m2l_lanes)
+static bool m2l_lanes(int P) { return P == 21 || P == 25 || P == 31 || P == 41; }
+static bool one_stream(long leaves, int P, int mixed_mode) {
+  if (mixed_mode == 1) return m2l_lanes(P) && leaves * P * P < kTwoStreamBf16Work;
+  if (mixed_mode == 2 && !m2l_lanes(P)) return leaves < kTwoStreamInt8General;
+  return leaves < kTwoStreamLeaves;
+}
+// Below this many leaves the bf16 slices are cut after the moments and P2L
+// runs on the caller's stream; from it on they are cut beside the moments and
+// P2L runs ahead of the near field.  us per execute of the two: 4198 leaves
+// p = 20 161 and 170, p = 24 165 and 170, p = 30 188 and 195; 2050 leaves p =
+// 24 135 and 143; 10558 leaves p = 24 279 and 283; 14254 leaves p = 20 401 and
+// 357, p = 24 380 and 375.  (Slices beside the moments with P2L on the
+// caller's stream, as for int8: 183, 183, 208; 133; 299; 368, 378.)
+constexpr int kBf16SlicesFirst = 12000;
 // list-2 groups up to which M2L runs one work-group per chunk of outputs: two
 // groups per CU, beyond which the chunks' repeated source loads cost more than
 // the idle CUs (64 leaves 48 -> 45 us, ten trees of up to a few hundred leaves
@@ -1913,19 +1938,24 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   // fork: P2L and the near field on the side stream, concurrent with the
   // upward pass, M2L and the downward pass on the caller's stream.  The
   // persistent near-field grids are bounded (about two work-groups per CU,
-  // looping over the tiles).  With a mixed near field the slices of f^e are
-  // cut beside the moments, else the side stream starts after them.
+  // looping over the tiles).  The side stream starts after the moments, or
+  // beside them if the slices of a mixed near field are cut there.
   // Small trees stay on the caller's stream: a wait between streams costs
   // about 7 us, more than their near field takes beside the other kernels.
-  const bool one = !H.ts && (long)L * nrhs < kTwoStreamLeaves;
-  hipStream_t side = one ? s : p->side;
   const bool mixed = H.precision >= 1 && !H.ts && !(H.ml_cfg.empty() && H.mt_cfg.empty());
-  if (mixed) {
+  const bool one = !H.ts && one_stream((long)L * nrhs, P, mixed ? H.precision : 0);
+  hipStream_t side = one ? s : p->side;
+  const bool slices_late = mixed && H.precision == 1 && L < kBf16SlicesFirst;
+  const bool p2l_caller = mixed && (H.precision == 2 || slices_late);  // else on the side stream
+  auto split = [&]() -> int {
+    return H.precision == 2 ? launch_split_f8(p, fe, nrhs, side, err) : launch_split_fx(p, fe, nrhs, side, err);
+  };
+  if (mixed && !slices_late) {
     if (!one) {
       VFX_HIP(hipEventRecord(p->fork_ev, s));
       VFX_HIP(hipStreamWaitEvent(side, p->fork_ev, 0));
     }
-    int rc = H.precision == 2 ? launch_split_f8(p, fe, nrhs, side, err) : launch_split_fx(p, fe, nrhs, side, err);
+    int rc = split();
     if (rc) return rc;
   }
   // exterior moments and multipoles of the leaves
@@ -1937,18 +1967,22 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     VFX_HIP(hipEventRecord(p->mom_ev, s));
     VFX_HIP(hipStreamWaitEvent(side, p->mom_ev, 0));
   }
+  if (slices_late) {
+    int rc = split();
+    if (rc) return rc;
+  }
   // P2L first on the side stream (M2L on the caller's stream waits for it),
-  // then the near field.  With a mixed near field P2L runs before M2L on the
-  // caller's stream instead: the mixed kernel holds its full register file
-  // and is best started beside the upward pass (14254 leaves, int8: 337 ->
-  // 323 us); the FP64 near field is better after P2L (the same tree: 259
-  // against 263 us).
+  // then the near field.  With a mixed near field P2L mostly runs before M2L
+  // on the caller's stream instead: the mixed kernel holds its full register
+  // file and is best started beside the upward pass (14254 leaves, int8: 337
+  // -> 323 us; bf16: kBf16SlicesFirst); the FP64 near field is better after
+  // P2L (the same tree: 259 against 263 us).
   MARK(10, side);
-  if (H.nlev > 2 && !mixed) {
+  if (H.nlev > 2 && !p2l_caller) {
     int rc = launch_p2l(p, nrhs, side, err);
     if (rc) return rc;
   }
-  if (!one && !mixed) VFX_HIP(hipEventRecord(p->p2l_ev, side));
+  if (!one && !p2l_caller) VFX_HIP(hipEventRecord(p->p2l_ev, side));
   MARK(5, side);
   if (H.ts) {
     // target-stationary near field: the factor products Z = (W_b P_g^T) f
@@ -2017,11 +2051,11 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   MARK(11, side);
   if (!one) VFX_HIP(hipEventRecord(p->join_ev, side));
   if (H.nlev > 2) {
-    if (mixed) {
+    if (p2l_caller) {
       int rc = launch_p2l(p, nrhs, s, err);
       if (rc) return rc;
     }
-    if (!one && !mixed) VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
+    if (!one && !p2l_caller) VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
     const int ng = (int)H.m2l_grp.size() - 1;
     const bool split = (long)ng * nrhs <= kM2LSplitGroups;
     if (ng > 0) {
