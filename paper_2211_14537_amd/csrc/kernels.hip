@@ -59,11 +59,15 @@ __device__ __forceinline__ double box_side(double root, int level) { return ldex
 // start (two waves: indices/geometry, then the data they point to), so the
 // work-group's critical path holds few memory round trips.  The time of one
 // work-group is the time of the phase on small trees: with at most one cut
-// leaf per CU it has 1024 threads (A1 in one pass, four targets at a time),
-// with at most two 512; more cut leaves run at 256, six work-groups per CU,
-// where the HBM stream of the operators is the bound.
+// leaf per CU it has 1024 threads (A1 in one pass, four targets at a time);
+// more cut leaves run at 256, six work-groups per CU, where the HBM stream of
+// the operators becomes the bound.  The phase in us at 256, 512 and 1024
+// threads, K = 16 (K = 8): 156 cut leaves 22.8, 20.9, 17.0 (16.9, 14.1, 12.2);
+// 196: 24.6, 22.6, 19.0 (19.1, 17.2, 15.1); 308: 27.0, 28.7, 27.7 (20.9, 21.3,
+// 22.5); 386: 28.1, 29.1, 28.7 (21.8, 22.4, 23.9); 612: 34.9, 44.0, 40.0 (25.2,
+// 35.5, 32.5).
 constexpr int kExtTgtMax = 16;  // targets whose geometry is staged in LDS
-constexpr int kExtOnePerCu = 256;  // 64 leaves, 20 cut: 54.4 -> 47.7 us; ten small trees: 889 -> 834 us
+constexpr int kExtOnePerCu = 256;
 
 // f^e of the leaves no extension list writes, 16-byte pieces e0, e0 +
 // step, ... below e1 (piece e: right-hand side e / half, element 2 (e mod
@@ -94,7 +98,7 @@ __device__ __forceinline__ void fe_init_range(long e0, long e1, long step, int n
 }
 
 // KT, KBT: compile-time K and Kbar (0: as passed): the index divisions of the
-// evaluation by run-time sizes cost a 64-leaf tree 2 us of 45, 2510 leaves
+// evaluation by run-time sizes cost a 64-leaf tree 2 us of 45, 4207 leaves
 // 4 us of 139
 template <int NT, int KT, int KBT>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 ? 6 : 4))) k_extension(
@@ -1906,7 +1910,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
       if (rc) return rc;
     }
     const int blocks1 = gemm ? 0 : ext_blocks;
-    const int nt = blocks1 > 0 && blocks1 <= kExtOnePerCu ? 1024 : blocks1 > 0 && blocks1 <= 2 * kExtOnePerCu ? 512 : 256;
+    const int nt = blocks1 > 0 && blocks1 <= kExtOnePerCu ? 1024 : 256;
     const int copy_blocks = (int)std::min<long>((pieces + nt - 1) / nt, 262144 / nt);
 #define VFX_EXT(NTV)                \
   if (T.Kbar != 12)                 \
@@ -1925,8 +1929,6 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
                      DT.AbarT, DT.cbar, f_cut, fe, nrhs, sFC, sFL, blocks1, L, D.fe_src, f_leaf)
     if (nt == 1024) {
       VFX_EXT(1024);
-    } else if (nt == 512) {
-      VFX_EXT(512);
     } else {
       VFX_EXT(256);
     }
