@@ -656,6 +656,8 @@ def main():
     for k, (fl_, by_, stream_) in work.items():
         if args.precision != "fp64" and k in ("near_lowrank", "near_dense"):
             continue  # int8 or bf16 kernels: not an FP64 roofline
+        if args.precision == "mixed" and k == "p2l":
+            stream_ = "caller"  # ahead of M2L
         t_roof = max(fl_ / (FP64_PEAK_TFLOPS * 1e12), by_ / (HBM_PEAK_GBS * 1e9))
         ms = phases.get(k)
         rows.append({"phase": k, "kernel": kernels[k][0], "stream": stream_, "flops": fl_, "bytes": by_,

@@ -351,27 +351,28 @@ int vfx_graph_end(void* stream, vfx_graph** out);
 int vfx_graph_launch(vfx_graph* graph, void* stream);
 int vfx_graph_destroy(vfx_graph* graph);
 
-/* Per-phase timing with HIP events.  The near-field kernels run on a side
- * stream of the plan (default priority), forked from `stream` after the
- * extension and joined before the far-field kernel; their phases are timed
- * with events on that side stream, the others on `stream`.  While enabled,
- * every vfx_execute records its events (at most 4096 executes are recorded;
- * enabling again restarts the count).  The query synchronises on the last
- * recorded event and returns, averaged over the recorded executes, the
- * milliseconds of eleven phases:
+/* Per-phase timing with HIP events.  On all but small trees the near-field
+ * kernels run on a side stream of the plan (default priority), forked from
+ * `stream` and joined before the far-field kernel; small trees run everything
+ * on `stream`.  Each phase is timed with events around its launches on the
+ * stream they go to.  While enabled, every vfx_execute records its events (at
+ * most 4096 executes are recorded; enabling again restarts the count).  The
+ * query synchronises on the last recorded event and returns, averaged over the
+ * recorded executes, the milliseconds of eleven phases (0 for a phase that
+ * launches nothing):
  *   ms[0] extension (the cut-leaf kernel, with the f^e initialisation of
  *         the other leaves)
  *   ms[1] exterior moments, P2M and the upward pass
- *   ms[2] M2L (with the wait for P2L, or with P2L itself if pairs are in
- *         mixed precision)
+ *   ms[2] M2L (with the wait for P2L where that runs on the side stream)
  *   ms[3] downward pass (leaf local expansions)
  *   ms[4] near field, first kernel (side stream): the FP64 pairs, or on
  *         the target-stationary path (FP64, K = 16) the factor products
- *   ms[5] near field, second kernel (side stream): the pairs in mixed
- *         precision, or the per-target-group kernel of the target-stationary
- *         path
+ *   ms[5] near field, second kernel (side stream): the slices and the pairs
+ *         in mixed precision, or the per-target-group kernel of the
+ *         target-stationary path
  *   ms[6] far field (list-1 and list-3 sums, L2P)   ms[7] total
- *   ms[8] P2L, list-4 products (side stream; 0 with pairs in mixed precision)
+ *   ms[8] P2L, list-4 products (side stream; with pairs in mixed precision
+ *         mostly `stream`, before M2L)
  *   ms[9] M2P, list-3 products (side stream, after the near field and the
  *         upward pass)
  *   ms[10] f^e initialisation: 0 (it runs inside the extension launch,

@@ -547,21 +547,25 @@ int vfx_plan_timings(vfx_plan* plan, double* ms, int n_out) {
   constexpr int NP = 11;  // phases
   if (!plan || !ms || n_out < NP) return fail(VFX_EINVAL, "vfx_plan_timings: bad argument");
   vfx::Plan& p = plan->p;
-  constexpr int NE = vfx::Plan::kEvents;
+  using P = vfx::Plan;
   if (p.n_timed == 0) return fail(VFX_EINVAL, "vfx_plan_timings: no timed execute recorded");
-  hipError_t e = hipEventSynchronize(p.ev[(size_t)(p.n_timed - 1) * NE + 9]);
+  hipError_t e = hipEventSynchronize(p.ev[(size_t)(p.n_timed - 1) * P::kEvents + P::evEnd]);
   if (e != hipSuccess) return fail(VFX_EHIP, std::string("vfx_plan_timings: ") + hipGetErrorString(e));
-  // phase k runs from event a[k] to event b[k]
-  static const int a_[NP] = {12, 1, 2, 3, 5, 6, 8, 0, 10, 13, 0};
-  static const int b_[NP] = {1, 2, 3, 4, 6, 7, 9, 9, 5, 11, 12};
+  // phase, from event, to event; an interval counts where both were recorded
+  static const int iv[][3] = {
+      {0, P::evStart, P::evExt},   {1, P::evMom0, P::evMom1},   {1, P::evUp0, P::evUp1},   {2, P::evM2l0, P::evM2l1},
+      {3, P::evM2l1, P::evDown1},  {4, P::evNear0, P::evNear1}, {5, P::evSlice0, P::evSlice1},
+      {5, P::evNear1, P::evNear2}, {6, P::evFar0, P::evEnd},    {7, P::evStart, P::evEnd}, {8, P::evP2l0, P::evP2l1},
+      {9, P::evM2p0, P::evM2p1}};
   double acc[NP] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   for (int r = 0; r < p.n_timed; ++r) {
-    const hipEvent_t* ev = &p.ev[(size_t)r * NE];
-    for (int k = 0; k < NP; ++k) {
+    const hipEvent_t* ev = &p.ev[(size_t)r * P::kEvents];
+    for (const int* v : iv) {
+      if (!(p.ev_set[r] >> v[1] & p.ev_set[r] >> v[2] & 1)) continue;
       float t = 0;
-      e = hipEventElapsedTime(&t, ev[a_[k]], ev[b_[k]]);
+      e = hipEventElapsedTime(&t, ev[v[1]], ev[v[2]]);
       if (e != hipSuccess) return fail(VFX_EHIP, std::string("vfx_plan_timings: ") + hipGetErrorString(e));
-      acc[k] += t;
+      acc[v[0]] += t;
     }
   }
   for (int k = 0; k < NP; ++k) ms[k] = acc[k] / p.n_timed;

@@ -1870,15 +1870,10 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
       p->ev.push_back(e);
     }
   }
-  // events on the caller's stream: 0 start, 12 after f^e initialisation, 1
-  // after the extension, 2 after P2M and the upward pass, 3 after M2L, 4
-  // after the downward pass, 8 after the join, 9 end; on the side stream: 10
-  // start, 5 after P2L, 6 after the first near-field kernel (the FP64 pairs,
-  // or the factor products of the target-stationary path), 7 after the
-  // second (the pairs in mixed precision, or the per-target-group kernel), 13 after the wait
-  // for the upward pass, 11 after M2P
+  if (timed) p->ev_set.resize(p->n_timed + 1), p->ev_set.back() = 0;
   auto mark = [&](int k, hipStream_t st) -> int {
     if (timed) {
+      p->ev_set[p->n_timed] |= 1u << k;
       hipError_t e = hipEventRecord(p->ev[ev0 + k], st);
       if (e != hipSuccess) {
         err = std::string("hipEventRecord: ") + hipGetErrorString(e);
@@ -1892,8 +1887,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     int rc_ = mark(k, st);   \
     if (rc_) return rc_;     \
   } while (0)
-  MARK(0, s);
-  MARK(12, s);
+  MARK(Plan::evStart, s);
   {
     // the extension of every cut leaf, and in the same launch the f^e
     // initialisation of the other leaves
@@ -1936,7 +1930,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
 #undef VFX_EXTK
   }
   VFX_HIP(hipGetLastError());
-  MARK(1, s);
+  MARK(Plan::evExt, s);
   // fork: P2L and the near field on the side stream, concurrent with the
   // upward pass, M2L and the downward pass on the caller's stream.  The
   // persistent near-field grids are bounded (about two work-groups per CU,
@@ -1950,7 +1944,17 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   const bool slices_late = mixed && H.precision == 1 && L < kBf16SlicesFirst;
   const bool p2l_caller = mixed && (H.precision == 2 || slices_late);  // else on the side stream
   auto split = [&]() -> int {
-    return H.precision == 2 ? launch_split_f8(p, fe, nrhs, side, err) : launch_split_fx(p, fe, nrhs, side, err);
+    MARK(Plan::evSlice0, side);
+    int rc = H.precision == 2 ? launch_split_f8(p, fe, nrhs, side, err) : launch_split_fx(p, fe, nrhs, side, err);
+    if (!rc) rc = mark(Plan::evSlice1, side);
+    return rc;
+  };
+  auto p2l = [&](hipStream_t st) -> int {
+    if (H.t4_cfg.empty()) return VFX_OK;
+    MARK(Plan::evP2l0, st);
+    int rc = launch_p2l(p, nrhs, st, err);
+    if (!rc) rc = mark(Plan::evP2l1, st);
+    return rc;
   };
   if (mixed && !slices_late) {
     if (!one) {
@@ -1961,10 +1965,12 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     if (rc) return rc;
   }
   // exterior moments and multipoles of the leaves
+  MARK(Plan::evMom0, s);
   {
     int rc = launch_moments(p, fe, nrhs, s, err);
     if (rc) return rc;
   }
+  MARK(Plan::evMom1, s);
   if (!one) {
     VFX_HIP(hipEventRecord(p->mom_ev, s));
     VFX_HIP(hipStreamWaitEvent(side, p->mom_ev, 0));
@@ -1979,31 +1985,32 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
   // file and is best started beside the upward pass (14254 leaves, int8: 337
   // -> 323 us; bf16: kBf16SlicesFirst); the FP64 near field is better after
   // P2L (the same tree: 259 against 263 us).
-  MARK(10, side);
   if (H.nlev > 2 && !p2l_caller) {
-    int rc = launch_p2l(p, nrhs, side, err);
+    int rc = p2l(side);
     if (rc) return rc;
   }
   if (!one && !p2l_caller) VFX_HIP(hipEventRecord(p->p2l_ev, side));
-  MARK(5, side);
   if (H.ts) {
     // target-stationary near field: the factor products Z = (W_b P_g^T) f
     // of every non-self pair (table GEMM over the configuration-major
     // tiles), then the per-target-group kernel, which leaves h^2 times each
     // leaf's list-1 table sum in V
+    MARK(Plan::evNear0, side);
     if (!H.nl_cfg.empty())
       launch_gemm<256, 4>((int)H.nl_cfg.size(), 4, D.nl_cfg, D.nl_first, D.nl_count, D.np_src, DT.lr_Wp, fe,
                           D.near_z, side, p->tune.near_wgs, R, sFL, sNZ);
     VFX_HIP(hipGetLastError());
-    MARK(6, side);
+    MARK(Plan::evNear1, side);
     {
       int rc = launch_near_ts(p, fe, V, nrhs, p->tune.near_wgs, side, err);
       if (rc) return rc;
     }
+    MARK(Plan::evNear2, side);
   } else {
+    if (!H.sy_tgt.empty() || !H.nl_cfg.empty()) MARK(Plan::evNear0, side);
     int rc = launch_near_sym(p, fe, nrhs, p->tune.near_wgs, side, err);
     if (rc) return rc;
-    MARK(6, side);
+    MARK(Plan::evNear1, side);
     if (mixed) {
       // pairs in mixed precision: the low-rank and self products of the
       // fixed-point bf16 (mode 1) or int8 (mode 2) slices (FP64 results, rows
@@ -2011,11 +2018,12 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
       rc = H.precision == 2 ? launch_near_f8(p, nrhs, p->tune.near_wgs, side, err)
                             : launch_near_fx(p, nrhs, p->tune.near_wgs, side, err);
       if (rc) return rc;
+      MARK(Plan::evNear2, side);
     }
   }
   VFX_HIP(hipGetLastError());
-  MARK(7, side);
   if (!H.up_grp.empty()) {
+    MARK(Plan::evUp0, s);
     const int ng = (int)H.up_grp.size() / 5;
 #define VFX_UP(PMV, EX)                                                                                            \
   hipLaunchKernelGGL((k_up<PMV, EX>), dim3(ng, R, (P + 7) / 8), dim3(64), 0, s, P, T.root_size, D.up_grp, D.up_box, D.up_ptr,  \
@@ -2037,26 +2045,27 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     if (!H.up_split.empty())
       hipLaunchKernelGGL(k_up_sum, dim3((int)H.up_split.size() / 3, R), dim3(64), 0, s, P, D.up_split, D.up_part,
                          D.mpole, sUP, sMP);
+    MARK(Plan::evUp1, s);
   }
   VFX_HIP(hipGetLastError());
-  MARK(2, s);
   // M2P for list 3 on the side stream, behind the near field, once the
   // upward pass is done; the side stream then joins the caller's
   if (!one) {
     VFX_HIP(hipEventRecord(p->up_ev, s));
     VFX_HIP(hipStreamWaitEvent(side, p->up_ev, 0));
   }
-  MARK(13, side);
+  if (!H.t3_cfg.empty()) MARK(Plan::evM2p0, side);
   m2p_gemm(n, T.p2l_rows, 2 * P, (int)H.t3_cfg.size(), D.t3_cfg, D.t3_first, D.t3_count, D.p3_src, DT.m2p_gemm,
            (const double*)D.mpole, D.m2p_y, side, R, 2 * sMP, sM3);
   VFX_HIP(hipGetLastError());
-  MARK(11, side);
+  if (!H.t3_cfg.empty()) MARK(Plan::evM2p1, side);
   if (!one) VFX_HIP(hipEventRecord(p->join_ev, side));
   if (H.nlev > 2) {
     if (p2l_caller) {
-      int rc = launch_p2l(p, nrhs, s, err);
+      int rc = p2l(s);
       if (rc) return rc;
     }
+    MARK(Plan::evM2l0, s);
     if (!one && !p2l_caller) VFX_HIP(hipStreamWaitEvent(s, p->p2l_ev, 0));  // list-4 products from the side stream
     const int ng = (int)H.m2l_grp.size() - 1;
     const bool split = (long)ng * nrhs <= kM2LSplitGroups;
@@ -2092,7 +2101,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
     }
   }
   VFX_HIP(hipGetLastError());
-  MARK(3, s);
+  MARK(Plan::evM2l1, s);
   // full local expansions of the leaves (downward pass)
   {
     const int ng = (int)H.dn_grp.size() - 1;
@@ -2115,9 +2124,9 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
 #undef VFX_DOWN
   }
   VFX_HIP(hipGetLastError());
-  MARK(4, s);
+  MARK(Plan::evDown1, s);
   if (!one) VFX_HIP(hipStreamWaitEvent(s, p->join_ev, 0));  // join
-  MARK(8, s);
+  MARK(Plan::evFar0, s);
   {
     const FarArgs A{L,      P,        T.root_size, H.ts,     D.leaf_box,   D.box_level, DT.t,    D.l3_ptr, D.l3_src,
                     D.l3_slot, D.m2p_y, D.locf,  D.mpole, D.l1_ptr, D.l1_srcbox, D.sy_row, D.ysym, D.y_ptr,
@@ -2137,7 +2146,7 @@ int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut,
 #undef VFX_FAR
   }
   VFX_HIP(hipGetLastError());
-  MARK(9, s);
+  MARK(Plan::evEnd, s);
   if (timed) p->n_timed++;
   return VFX_OK;
 }

@@ -309,8 +309,21 @@ struct Plan {
   // for the whole side stream (join_ev)
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr, p2l_ev = nullptr, up_ev = nullptr, mom_ev = nullptr;
-  // per-phase timing: one set of kEvents events per timed execute
-  static constexpr int kEvents = 14;
+  // per-phase timing: one set of kEvents events per timed execute; a phase
+  // that launches nothing records none (ev_set: the events recorded, a bit
+  // each).  Every phase has a beginning of its own where another phase may
+  // come between on the same stream.
+  enum Event {
+    evStart, evExt,      // extension
+    evSlice0, evSlice1,  // slices of the mixed near field
+    evMom0, evMom1,      // moments and P2M
+    evP2l0, evP2l1,
+    evNear0, evNear1, evNear2,  // first and second near-field kernel
+    evUp0, evUp1, evM2p0, evM2p1, evM2l0, evM2l1,
+    evDown1,             // downward pass, from evM2l1
+    evFar0, evEnd,       // far field
+    kEvents
+  };
   // launch parameters chosen by vfx_plan_autotune
   struct Tune {
     int near_wgs = 512;  // work-group cap of the persistent near-field kernels (2 per CU,
@@ -319,6 +332,7 @@ struct Plan {
   } tune;
   bool timing = false;
   std::vector<hipEvent_t> ev;   // kEvents * capacity
+  std::vector<uint32_t> ev_set; // per timed execute
   int n_timed = 0;
   uint64_t id = 0, gen = 0;     // identity and generation of the device buffers
 };
