@@ -1,4 +1,5 @@
 // C-ABI entry points of the vfx library (declared in include/vfx.h).
+#include <algorithm>
 #include <cstdint>
 #include <cstring>
 #include <exception>
@@ -573,9 +574,7 @@ int vfx_plan_timings(vfx_plan* plan, double* ms, int n_out) {
   return VFX_OK;
 }
 
-int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64_t count) {
-  if (!ctx || !out) return fail(VFX_EINVAL, "vfx_debug_table: null argument");
-  const vfx::Tables& T = ctx->c.T;
+static int debug_table(const vfx::Tables& T, int which, int index, double* out, int64_t count) {
   const int64_t n = T.n, P = T.p + 1;
   const double* src = nullptr;
   int64_t size = 0;
@@ -695,15 +694,13 @@ int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64
       break;
     }
     case 19: {  // table 3 as a real operand, [j][2l, 2l + 1], rows padded
-      static thread_local std::vector<double> v;
-      const size_t R = T.p2l_rows, P = T.p + 1;
-      v.assign((size_t)vfx::kP2LSlots * n * R, 0.0);
+      const size_t R = T.p2l_rows, P = T.p + 1, all = (size_t)vfx::kP2LSlots * n * R;
+      if ((int64_t)all != count) break;
+      std::fill(out, out + all, 0.0);
       for (size_t sl = 0; sl < (size_t)vfx::kP2LSlots * P; ++sl)
         for (size_t j = 0; j < (size_t)n; ++j)
-          for (int c = 0; c < 2; ++c) v[(sl / P * n + j) * R + 2 * (sl % P) + c] = T.p2l[2 * (sl * n + j) + c];
-      src = v.data();
-      size = (int64_t)v.size();
-      break;
+          for (int c = 0; c < 2; ++c) out[(sl / P * n + j) * R + 2 * (sl % P) + c] = T.p2l[2 * (sl * n + j) + c];
+      return VFX_OK;
     }
     case 23:
       if (index < 0 || index >= vfx::kP2LSlots) break;
@@ -723,6 +720,15 @@ int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64
   if (!src || size != count) return fail(VFX_EINVAL, "vfx_debug_table: bad table, index or count");
   std::memcpy(out, src, sizeof(double) * size);
   return VFX_OK;
+}
+
+int vfx_debug_table(const vfx_ctx* ctx, int which, int index, double* out, int64_t count) {
+  if (!ctx || !out) return fail(VFX_EINVAL, "vfx_debug_table: null argument");
+  try {
+    return debug_table(ctx->c.T, which, index, out, count);
+  } catch (const std::bad_alloc&) {
+    return fail(VFX_ENOMEM, "vfx_debug_table: out of host memory");
+  }
 }
 
 int vfx_plan_lists(const vfx_plan* plan, int which, int32_t* ptr, int32_t* src, int32_t* cfg) {
