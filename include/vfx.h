@@ -307,13 +307,14 @@ int vfx_plan_factor_gpu(vfx_plan* plan, void* stream);
 int vfx_execute_batch(vfx_plan* plan, int nrhs, const double* f_leaf, const double* f_cut, double* fe_out,
                       double* V_out, void* stream);
 
-/* Launch-parameter autotuner: times `reps` executes of the given batch
- * for each candidate (work-group cap of the persistent near-field kernels
- * 256/512/768/1024; dense_mtb 4/8 at
- * K = 16, which changes nothing at present) with HIP events on `stream` and keeps the fastest for later
- * executes of the plan; choice[0..1] (optional) receive it.  The choices
- * change only how work is distributed, not the arithmetic: results are
- * bitwise independent of them.  The buffers are overwritten. */
+/* Launch-parameter autotuner: at K = 16 times `reps` executes of the given
+ * batch for each work-group cap 256/512/768/1024 of the persistent near-field
+ * kernels with HIP events on `stream` and keeps the fastest for later executes
+ * of the plan; at other K, where no kernel depends on the cap, it stays as it
+ * is and the batch is executed once.  choice[0] (optional) receives the cap,
+ * choice[1] the value 4 of dense_mtb, which no present kernel depends on.  The
+ * cap changes only how work is distributed, not the arithmetic: results are
+ * bitwise independent of it.  The buffers are overwritten. */
 int vfx_plan_autotune(vfx_plan* plan, int nrhs, const double* f_leaf, const double* f_cut, double* fe_out,
                       double* V_out, void* stream, int reps, int32_t* choice);
 

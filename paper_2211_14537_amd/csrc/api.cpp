@@ -298,29 +298,29 @@ int vfx_plan_autotune(vfx_plan* plan, int nrhs, const double* f_leaf, const doub
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     return fail(VFX_EHIP, "vfx_plan_autotune: hipEventCreate failed");
+  // the cap matters to the K = 16 kernels only: other plans keep theirs and
+  // run once, so that a call that fails is still reported
   const int wgs[] = {256, 512, 768, 1024};
-  const int mtbs[] = {4, 8};
-  const int n_mtb = p.ctx->T.n == 256 ? 2 : 1;
+  const int nw = p.ctx->T.n == 256 ? 4 : 1;
   float best = 1e30f;
   vfx::Plan::Tune bt = p.tune;
+  bt.dense_mtb = 4;
   int rc = VFX_OK;
-  for (int a = 0; a < 4 && rc == VFX_OK; ++a)
-    for (int b = 0; b < n_mtb && rc == VFX_OK; ++b) {
-      p.tune.near_wgs = wgs[a];
-      p.tune.dense_mtb = mtbs[b];
-      rc = execute_checked(plan, nrhs, f_leaf, f_cut, fe_out, V_out, stream, "vfx_plan_autotune");  // warm-up
-      if (rc) break;
-      (void)hipEventRecord(e0, s);
-      for (int r = 0; r < reps && rc == VFX_OK; ++r)
-        rc = execute_checked(plan, nrhs, f_leaf, f_cut, fe_out, V_out, stream, "vfx_plan_autotune");
-      (void)hipEventRecord(e1, s);
-      if (hipEventSynchronize(e1) != hipSuccess) rc = fail(VFX_EHIP, "vfx_plan_autotune: event wait failed");
-      float ms = 0;
-      if (rc == VFX_OK && hipEventElapsedTime(&ms, e0, e1) == hipSuccess && ms < best) {
-        best = ms;
-        bt = p.tune;
-      }
+  for (int a = 0; a < nw && rc == VFX_OK; ++a) {
+    if (nw > 1) p.tune.near_wgs = wgs[a];
+    rc = execute_checked(plan, nrhs, f_leaf, f_cut, fe_out, V_out, stream, "vfx_plan_autotune");  // warm-up
+    if (rc || nw == 1) break;
+    (void)hipEventRecord(e0, s);
+    for (int r = 0; r < reps && rc == VFX_OK; ++r)
+      rc = execute_checked(plan, nrhs, f_leaf, f_cut, fe_out, V_out, stream, "vfx_plan_autotune");
+    (void)hipEventRecord(e1, s);
+    if (hipEventSynchronize(e1) != hipSuccess) rc = fail(VFX_EHIP, "vfx_plan_autotune: event wait failed");
+    float ms = 0;
+    if (rc == VFX_OK && hipEventElapsedTime(&ms, e0, e1) == hipSuccess && ms < best) {
+      best = ms;
+      bt.near_wgs = p.tune.near_wgs;
     }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   p.tune = bt;
