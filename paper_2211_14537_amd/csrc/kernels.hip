@@ -348,11 +348,6 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-__device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
-  const double d = b.x * b.x + b.y * b.y;
-  return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
-}
-
 // calls f(integral_constant<int, I>) for I = I0 .. N-1 (ring indices in an
 // unrolled pipeline stay compile-time constants)
 template <int I, int N, class F>
@@ -895,16 +890,6 @@ __global__ void __launch_bounds__(64) k_up_sum(int P, const int* __restrict__ sp
   mpole[(size_t)sp[0] * P + l] = make_double2(r, i);
 }
 
-__device__ __forceinline__ double2 cpow(double2 z, int k) {
-  double2 r = make_double2(1.0, 0.0);
-  while (k) {
-    if (k & 1) r = cmul(r, z);
-    z = cmul(z, z);
-    k >>= 1;
-  }
-  return r;
-}
-
 // -------------------------------------------------------------------------
 // Downward pass without the level-by-level chain: the local expansion of a
 // leaf b is its own (M2L + P2L) part plus the own parts of its ancestors A
@@ -1442,12 +1427,6 @@ static int upload(T** dst, const T* src, size_t count, std::string& err) {
     if (rc_) return rc_;                                                   \
   } while (0)
 
-static std::vector<double2> as_complex(const std::vector<double>& src) {
-  std::vector<double2> o(src.size() / 2);
-  for (size_t i = 0; i < o.size(); ++i) o[i] = make_double2(src[2 * i], src[2 * i + 1]);
-  return o;
-}
-
 // Rows of K^2 target nodes in folded form: y_q of a quadrant node is a quarter
 // of the signed sum of its four images (q = 2 qx + qy).
 static std::vector<double> fold_rows(const std::vector<double>& v, int K) {
@@ -1468,9 +1447,7 @@ static std::vector<double> fold_rows(const std::vector<double>& v, int K) {
 int upload_tables(Context* c, std::string& err) {
   const Tables& T = c->T;
   DeviceTables& D = c->D;
-  const int n = T.n, P = T.p + 1;
   UP(D.t, T.t);
-  UP(D.tbar, T.tbar);
   UP(D.w2, T.w2);
   UP(D.AbarT, T.AbarT);
   UP(D.A, T.A);
@@ -1500,38 +1477,10 @@ int upload_tables(Context* c, std::string& err) {
   UP(D.f8_Aexp, T.f8_Aexp);
   UP(D.p2l_gemm, T.p2l_gemm);
   UP(D.m2p_gemm, m2p_f);
-  UP(D.pas_m2l, T.pas_m2l);
   UP(D.pas_m2l_t, T.pas_m2l_t);
   UP(D.pas_m2m_t, T.pas_m2m_t);
   UP(D.pas_l2l_t, T.pas_l2l_t);
-  UP(D.pas_m2m, T.pas_m2m);
-  UP(D.pas_l2l, T.pas_l2l);
   UP(D.m2l_logd, T.m2l_logd);
-  std::vector<double2> v;
-  // p2m [k][j] -> [j][k]
-  v.assign((size_t)n * P, make_double2(0, 0));
-  for (int k = 0; k < P; ++k)
-    for (int j = 0; j < n; ++j)
-      v[(size_t)j * P + k] = make_double2(T.p2m[2 * ((size_t)k * n + j)], T.p2m[2 * ((size_t)k * n + j) + 1]);
-  UP(D.p2m, v);
-  // l2p [i][l] -> [l][i]
-  v.assign((size_t)n * P, make_double2(0, 0));
-  for (int i = 0; i < n; ++i)
-    for (int l = 0; l < P; ++l)
-      v[(size_t)l * n + i] = make_double2(T.l2p[2 * ((size_t)i * P + l)], T.l2p[2 * ((size_t)i * P + l) + 1]);
-  UP(D.l2p, v);
-  v = as_complex(T.m2l_tpow);
-  UP(D.m2l_tpow, v);
-  v = as_complex(T.m2l_tneg);
-  UP(D.m2l_tneg, v);
-  v = as_complex(T.m2m_in);
-  UP(D.m2m_in, v);
-  v = as_complex(T.m2m_out);
-  UP(D.m2m_out, v);
-  v = as_complex(T.l2l_in);
-  UP(D.l2l_in, v);
-  v = as_complex(T.l2l_out);
-  UP(D.l2l_out, v);
   VFX_HIP(hipGetDevice(&D.device));
   D.ready = true;
   return VFX_OK;
@@ -1540,13 +1489,10 @@ int upload_tables(Context* c, std::string& err) {
 void free_tables_device(Context* c) {
   DeviceTables& D = c->D;
   c->gen++;
-  void* ptrs[] = {D.t,        D.tbar,     D.w2,       D.AbarT,   D.cbar,     D.mom_T,   D.sym_T,     D.pair_T,   D.A,
-                  D.p2m,      D.l2p,      D.m2m,      D.l2l,     D.m2l,      D.p2l,     D.p2l_area,
-                  D.pas_m2l,  D.pas_m2m,  D.pas_l2l,  D.m2l_logd, D.p2l_gemm, D.m2p_gemm, D.m2l_tpow, D.m2l_tneg,
-                  D.m2m_in,   D.m2m_out,  D.l2l_in,   D.l2l_out,  D.pas_m2l_t, D.pas_m2m_t, D.pas_l2l_t,
-                  D.lr_R,     D.fx_W,     D.fx_Q,     D.fx_A,     D.fx_Wexp,
-                  D.fx_Qexp,  D.fx_Aexp,  D.f8_W,     D.f8_Q,     D.f8_A,     D.f8_Wexp,  D.f8_Qexp,  D.f8_Aexp,
-                  D.cls_R,    D.lr_Wp,    D.cls_QT,   D.self_T};
+  void* ptrs[] = {D.t, D.w2, D.AbarT, D.cbar, D.mom_T, D.sym_T, D.pair_T, D.A, D.m2l_logd, D.p2l_gemm, D.m2p_gemm,
+                  D.pas_m2l_t, D.pas_m2m_t, D.pas_l2l_t, D.lr_R, D.fx_W, D.fx_Q, D.fx_A, D.fx_Wexp, D.fx_Qexp,
+                  D.fx_Aexp, D.f8_W, D.f8_Q, D.f8_A, D.f8_Wexp, D.f8_Qexp, D.f8_Aexp, D.cls_R, D.lr_Wp, D.cls_QT,
+                  D.self_T};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   D = DeviceTables();
@@ -1621,11 +1567,9 @@ int upload_plan(Plan* p, std::string& err) {
     for (int b = 0; b < H.B; ++b) next[b] = H.box_leaf[b] >= 0 ? ~H.box_leaf[b] : H.box_child0[b];
     UP(D.box_next, next);
   }
-  UP(D.box_parent, H.box_parent);
   UP(D.box_cx, H.box_cx);
   UP(D.box_cy, H.box_cy);
   UP(D.leaf_box, H.leaf_box);
-  UP(D.kind, H.kind);
   {
     // where each leaf's f^e comes from: 2 an extension list, 1 f (regular), 0 zero
     std::vector<int8_t> src(H.L, 0);
@@ -1633,8 +1577,6 @@ int upload_plan(Plan* p, std::string& err) {
     UP(D.fe_src, src);
   }
   UP(D.l1_ptr, H.l1_ptr);
-  UP(D.l1_src, H.l1_src);
-  UP(D.l1_cfg, H.l1_cfg);
   UP(D.l1_srcbox, H.l1_srcbox);
   UP(D.l2_ptr, H.l2_ptr);
   UP(D.l2_src, H.l2_src);
@@ -1656,7 +1598,6 @@ int upload_plan(Plan* p, std::string& err) {
   UP(D.up_split, H.up_split);
   UP(D.l4_ptr, H.l4_ptr);
   UP(D.l4_src, H.l4_src);
-  UP(D.l4_cfg, H.l4_cfg);
   UP(D.np_src, H.np_src);
   UP(D.y_ptr, H.y_ptr);
   UP(D.y_slot, H.y_slot);
@@ -1688,7 +1629,6 @@ int upload_plan(Plan* p, std::string& err) {
   UP(D.t3_count, H.t3_count);
   UP(D.leaf_ids, H.leaf_ids);
 
-  UP(D.cut_leaf, H.cut_leaf);
   UP(D.ext_ptr, H.ext_ptr);
   UP(D.ext_tgt, H.ext_tgt);
   UP(D.ext_geo, H.ext_geo);
@@ -1721,14 +1661,14 @@ void free_plan_device(Plan* p) {
   if (D.ready) (void)hipDeviceSynchronize();  // no execute of this plan in flight
   p->gen++;
   free_rhs_buffers(D);
-  void* ptrs[] = {D.box_level, D.box_next, D.box_parent, D.box_cx, D.box_cy, D.leaf_box, D.kind, D.l1_ptr, D.l1_src,
-                  D.l1_cfg, D.l2_ptr, D.l2_src, D.l2_off, D.l3_ptr, D.l3_src, D.l4_ptr, D.l4_src, D.l4_cfg, D.np_src,
-                  D.y_ptr, D.y_slot, D.sy_nb, D.sy_row, D.p4_src, D.l4_slot, D.t4_cfg, D.t4_first, D.t4_count,
-                  D.cut_leaf, D.ext_ptr, D.ext_tgt, D.pinv_ptr, D.pinv_idx, D.pinv_val, D.sbar_given, D.leaf_ids,
-                  D.l2_tgt, D.m2l_grp, D.up_box, D.up_ptr, D.up_src, D.up_pos, D.up_split, D.up_grp, D.anc_ptr, D.anc,
-                  D.nl_cfg, D.nl_first, D.nl_count, D.l1_srcbox, D.ext_geo, D.anc_leaf, D.dn_grp, D.mt_cfg,
-                  D.mt_first, D.mt_count, D.ml_cfg, D.fac_ws, D.ml_first, D.ml_count, D.p3_src, D.l3_slot, D.t3_cfg,
-                  D.t3_first, D.t3_count, D.chg_part, D.ts_grp, D.ts_tcls, D.ts_row, D.ts_code, D.fe_src};
+  void* ptrs[] = {D.box_level, D.box_next, D.box_cx, D.box_cy, D.leaf_box, D.l1_ptr, D.l2_ptr, D.l2_src, D.l2_off,
+                  D.l3_ptr, D.l3_src, D.l4_ptr, D.l4_src, D.np_src, D.y_ptr, D.y_slot, D.sy_nb, D.sy_row, D.p4_src,
+                  D.l4_slot, D.t4_cfg, D.t4_first, D.t4_count, D.ext_ptr, D.ext_tgt, D.pinv_ptr, D.pinv_idx,
+                  D.pinv_val, D.sbar_given, D.leaf_ids, D.l2_tgt, D.m2l_grp, D.up_box, D.up_ptr, D.up_src, D.up_pos,
+                  D.up_split, D.up_grp, D.anc_ptr, D.anc, D.nl_cfg, D.nl_first, D.nl_count, D.l1_srcbox, D.ext_geo,
+                  D.anc_leaf, D.dn_grp, D.mt_cfg, D.mt_first, D.mt_count, D.ml_cfg, D.fac_ws, D.ml_first, D.ml_count,
+                  D.p3_src, D.l3_slot, D.t3_cfg, D.t3_first, D.t3_count, D.chg_part, D.ts_grp, D.ts_tcls, D.ts_row,
+                  D.ts_code, D.fe_src};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   D = DevicePlan();

@@ -104,7 +104,6 @@ int build_near_tiles(const Tables& T, HostPlan& H, int mode, int min_level, std:
   for (int g = 0; g < 2 * kNearConfigs; ++g) cnt[g + 1] += cnt[g];
   const int NP = cnt[2 * kNearConfigs];
   H.np_src.assign(NP, 0);
-  H.np_tgt.assign(NP, 0);
   H.l1_slot.assign(N1, -1);
   H.y_ptr.assign(L + 1, 0);
   H.y_slot.clear();
@@ -114,7 +113,6 @@ int build_near_tiles(const Tables& T, HostPlan& H, int mode, int min_level, std:
       if (sym(e)) continue;
       const int s = pos[2 * H.l1_cfg[e] + (mixed(e) ? 1 : 0)]++;
       H.np_src[s] = H.l1_src[e];
-      H.np_tgt[s] = leaf;
       H.l1_slot[e] = s;
       H.y_slot.push_back(mixed(e) ? ~s : s);
     }

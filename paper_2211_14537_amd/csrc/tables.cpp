@@ -349,12 +349,6 @@ static void build_near(Tables& T) {
   std::vector<double> C;
   cheb_coef_matrix(K, T.t, C);
   T.near.assign((size_t)kNearConfigs * n * n, 0.0);
-  T.near_s2.assign(kNearConfigs, 0.0);
-  for (int c = 0; c < kNearConfigs; ++c) {
-    double ox, oy, s;
-    near_config_geometry(c, &ox, &oy, &s);
-    T.near_s2[c] = s * s;
-  }
 #pragma omp parallel
   {
     std::vector<double> M(K * K), tmp(K * K);

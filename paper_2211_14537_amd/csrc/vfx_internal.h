@@ -79,7 +79,6 @@ struct Tables {
   std::vector<double> AbarT;           // nG x Kbar^2 (transposed Sbar rows)
   std::vector<double> cbar;            // Kbar x Kbar values -> coefficients
   std::vector<double> near;            // 33 x n x n, [c][j][i]
-  std::vector<double> near_s2;         // 33: (source side / target side)^2
   // low-rank near-field operators (near ~ Q W), see build_near_lowrank
   std::vector<int> lr_R, lr_rank;      // 33: padded rank (0 = dense), rank
   std::vector<double> lr_W;            // 33 x n x kNearLrMax, [c][j][a]
@@ -157,20 +156,15 @@ int pinv_jacobi(const double* A, int m, int n, double rel_cut, double* P);
 struct DeviceTables {
   bool ready = false;
   int device = -1;
-  double *t = nullptr, *tbar = nullptr, *w2 = nullptr, *AbarT = nullptr, *cbar = nullptr, *A = nullptr;
+  double *t = nullptr, *w2 = nullptr, *AbarT = nullptr, *cbar = nullptr, *A = nullptr;
   double *mom_T = nullptr, *sym_T = nullptr, *pair_T = nullptr;
   int* lr_R = nullptr;
   uint16_t *fx_W = nullptr, *fx_Q = nullptr, *fx_A = nullptr;
   int *fx_Wexp = nullptr, *fx_Qexp = nullptr, *fx_Aexp = nullptr;
   int8_t *f8_W = nullptr, *f8_Q = nullptr, *f8_A = nullptr;
   int *f8_Wexp = nullptr, *f8_Qexp = nullptr, *f8_Aexp = nullptr;
-  double2 *p2m = nullptr, *l2p = nullptr, *m2m = nullptr, *l2l = nullptr, *m2l = nullptr, *p2l = nullptr;
-  double* p2l_area = nullptr;
-  double *pas_m2l = nullptr, *pas_m2m = nullptr, *pas_l2l = nullptr, *m2l_logd = nullptr, *p2l_gemm = nullptr;
-  double* m2p_gemm = nullptr;
+  double *m2l_logd = nullptr, *p2l_gemm = nullptr, *m2p_gemm = nullptr;
   double *pas_m2l_t = nullptr, *pas_m2m_t = nullptr, *pas_l2l_t = nullptr;
-  double2 *m2l_tpow = nullptr, *m2l_tneg = nullptr, *m2m_in = nullptr, *m2m_out = nullptr, *l2l_in = nullptr,
-          *l2l_out = nullptr;
   int* cls_R = nullptr;
   double *lr_Wp = nullptr, *cls_QT = nullptr, *self_T = nullptr;
 };
@@ -216,7 +210,7 @@ struct HostPlan {
   // a configuration; l1_slot maps each per-target list-1 entry to its pair
   // index (-1 for none); y_ptr, y_slot: the pair rows of each target (~row for
   // a mixed-precision pair, whose row is in node order; the others are folded)
-  std::vector<int> np_src, np_tgt, l1_slot, y_ptr, y_slot;
+  std::vector<int> np_src, l1_slot, y_ptr, y_slot;
   std::vector<int> nl_cfg, nl_first, nl_count;  // FP64 tiles of <= 64 pairs
   // tiles of the pairs applied in mixed precision: self (mt), low rank (ml)
   std::vector<int> mt_cfg, mt_first, mt_count, ml_cfg, ml_first, ml_count;
@@ -252,12 +246,11 @@ struct HostPlan {
 
 struct DevicePlan {
   bool ready = false;
-  int *box_level = nullptr, *box_next = nullptr, *box_parent = nullptr;
+  int *box_level = nullptr, *box_next = nullptr;
   double *box_cx = nullptr, *box_cy = nullptr;
   int* leaf_box = nullptr;
-  int8_t* kind = nullptr;
   int8_t* fe_src = nullptr;  // per leaf: 2 written by the extension, 1 copied from f, 0 zero
-  int *l1_ptr = nullptr, *l1_src = nullptr, *l1_cfg = nullptr, *l1_srcbox = nullptr;
+  int *l1_ptr = nullptr, *l1_srcbox = nullptr;
   int *l2_ptr = nullptr, *l2_src = nullptr, *l2_off = nullptr, *l2_tgt = nullptr, *m2l_grp = nullptr;
   int *l3_ptr = nullptr, *l3_src = nullptr;
   int *up_box = nullptr, *up_ptr = nullptr, *up_src = nullptr, *up_pos = nullptr, *up_grp = nullptr,
@@ -265,7 +258,7 @@ struct DevicePlan {
   double2* up_part = nullptr;
   int *anc_ptr = nullptr, *anc = nullptr, *anc_leaf = nullptr, *dn_grp = nullptr;
   double2* locf = nullptr;  // full local expansion of every leaf, L x (p+1)  // partial multipoles of split boxes, up_slots x (p+1)
-  int *l4_ptr = nullptr, *l4_src = nullptr, *l4_cfg = nullptr;
+  int *l4_ptr = nullptr, *l4_src = nullptr;
   int *np_src = nullptr, *y_ptr = nullptr, *y_slot = nullptr, *sy_nb = nullptr, *sy_row = nullptr;
   // exterior moments (L + 1 rows, row L stays zero), and the same-level near
   // field of each target in folded form, one row per sy_tgt
@@ -288,7 +281,7 @@ struct DevicePlan {
   double* m2p_y = nullptr;   // per-entry M2P values at the target nodes, n_list3 x n
   double* chg_part = nullptr;  // net-charge block partials, kChargeBlocks x chg_cap
   int chg_cap = 0;
-  int *cut_leaf = nullptr, *ext_ptr = nullptr, *ext_tgt = nullptr, *pinv_ptr = nullptr;
+  int *ext_ptr = nullptr, *ext_tgt = nullptr, *pinv_ptr = nullptr;
   double* ext_geo = nullptr;
   uint16_t* pinv_idx = nullptr;
   double* pinv_val = nullptr;
