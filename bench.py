@@ -577,7 +577,7 @@ def main():
                     help="with --precision mixed: sources at this level or finer run mixed")
     ap.add_argument("--no-mixed", action="store_true", help="skip the mixed-precision sweep beside FP64")
     ap.add_argument("--near-mode", type=int, default=0, choices=(0, 1),
-                    help="FP64 near field: 0 pair-based, 1 target-stationary")
+                    help="FP64 near field: 0 from exterior moments, 1 target-stationary")
     ap.add_argument("--check-nodes", type=int, default=0,
                     help="without the CPU baseline: oracle accuracy check at this many seeded nodes")
     ap.add_argument("--batch", type=int, default=0,
@@ -587,7 +587,7 @@ def main():
     ap.add_argument("--autotune", action="store_true",
                     help="autotune the near-field launch parameters before the timed steps")
     ap.add_argument("--launch", default=None,
-                    help="near-field launch parameters W,M (work-group cap, dense row tiles) instead of autotuning")
+                    help="near-field launch parameters W,M (work-group cap; 4 or 8, without effect) instead of autotuning")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run one plain 256 MiB device copy (for HBM counter calibration)")
     args = ap.parse_args()

@@ -251,21 +251,18 @@ int vfx_net_charge_noalloc_max_rhs(void);
  * device and must not overlap an execute of the same plan. */
 int vfx_plan_set_precision(vfx_plan* plan, int mode, int min_level);
 
-/* Near-field strategy of the FP64 path at K = 16.  mode 0 (the default):
- * from
- * exterior moments - a leaf acts outside itself only through 4 (2K-4)
- * moments of its data, reflected neighbours share their operators, and a
- * target's same-level sources are summed in registers; pairs across levels
- * leave one row each, which the far-field kernel sums.  mode 1:
- * target-stationary - the products of each group of 16 consecutive target
+/* Near-field strategy of the FP64 path at K = 16.  mode 0 (the default): from
+ * exterior moments - a leaf acts outside itself only through 4 (2K-4) moments
+ * of its data, reflected neighbours share their operators, and a target's
+ * same-level sources are summed in registers; pairs across levels leave one
+ * row each, which the far-field kernel sums.  mode 1: target-stationary - the products of each group of 16 consecutive target
  * leaves are summed in registers and each leaf's near-field sum is written
  * once: the 32 neighbour configurations are folded onto six symmetry
  * classes of the square (T_c = P_g T_b P_g^T, Section 4 tables in
  * low-rank form Q_b W_b), a table GEMM forms every pair's W_b P_g^T f, and a
  * per-group kernel applies Q_b and the self table.  Both compute the same
  * sum (they differ by rounding); mode 1 does about three times the matrix
- * work.  Other K and
- * mixed pairs keep mode 0.  The plan's device data are rebuilt on the next
+ * work.  Other K and mixed pairs keep mode 0.  The plan's device data are rebuilt on the next
  * vfx_execute (graphs that captured it are invalidated); the call must not
  * overlap an execute of the same plan.  VFX_EINVAL for other modes. */
 int vfx_plan_set_near_mode(vfx_plan* plan, int mode);

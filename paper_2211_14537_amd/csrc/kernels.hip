@@ -1141,7 +1141,9 @@ __global__ void __launch_bounds__(256) k_far(FarArgs A) {
 // a row of the leaf is one contiguous load of the group, all K rows are in
 // flight together, and each lane forms one weight per axis.  (One thread per
 // point read 64 cache lines per load and formed 2K sines: 167 us for 200000
-// points at K = 16; now 32 us.)  The points of a wave are served in turn, so
+// points at K = 16; now 37 us alone.  The leaves' rows are 391 MB of reads from
+// the L2s, 91% hits, about 10 TB/s; the vector units are 43% busy; of the
+// waves' time a third is waiting for memory and half for issue.)  The points of a wave are served in turn, so
 // ppw is halved until there are kInterpWaves waves, about one full residency
 // (200000 points with the net charge after them: 50.4 us for 2048, 45.7 for
 // 4096, 44.0 for 8192, 46.9 for 16384).
@@ -1732,10 +1734,20 @@ static void m2p_gemm(int n, int kd, int P2, int ntiles, const int* cfg, const in
 #undef VFX_M2P
 }
 
-// leaves times right-hand sides from which the side stream pays (one MI355X,
-// one against two streams: 64 leaves 54 and 81-95 us, ten trees of 160 to 976
-// leaves in a graph 918 and 979 us, 2510 leaves 159 and 129 us, 3808 leaves
-// 100 and 101 us, 4207 leaves 155 and 145 us)
+// Leaves times right-hand sides from which the side stream is used: about where
+// it pays at K = 16 and p = 24.  One and two streams, us per execute of one
+// right-hand side:
+//   K = 16, p = 24   376 leaves 74, 91; 808: 89, 96; 976: 97, 99; 1114: 100, 98;
+//                    1840: 118, 110; 4198: 148, 135
+//   K = 16, p = 40   376: 101, 103; 532: 105, 106; 808: 124, 112; 976: 128, 117
+//   K = 12, p = 30   532: 87, 94; 850: 101, 97; 2056: 129, 116; 4204: 156, 137
+//   K = 8, p = 20    1495 to 1741: 71-75, 90-96; 2929: 93, 95; 4546: 100, 100
+//   K = 4, p = 17    472: 79, 93; 1696: 85, 98; 5788: 172, 181; 20668: 383, 388
+// and batches: 502 leaves x 5 at K = 12 159, 129; 136 x 7 at K = 16 110, 110, x
+// 12 212, 207; 145 x 7 at K = 8 85, 101, x 12 152, 160.  The near field grows
+// like K^4, the waits do not: at K <= 8 the tie is past 4000 leaves (the waits
+// of the two-stream form vary there from run to run by 20 us), at p = 40 near
+// 600.
 constexpr long kTwoStreamLeaves = 1000;
 // The same with mixed pairs.  The bf16 kernel takes 45 us and more on the
 // smallest trees, so it is worth hiding behind M2L as soon as that is long:
@@ -1762,10 +1774,13 @@ static bool one_stream(long leaves, int P, int mixed_mode) {
 // 357, p = 24 380 and 375.  (Slices beside the moments with P2L on the
 // caller's stream, as for int8: 183, 183, 208; 133; 299; 368, 378.)
 constexpr int kBf16SlicesFirst = 12000;
-// list-2 groups up to which M2L runs one work-group per chunk of outputs: two
-// groups per CU, beyond which the chunks' repeated source loads cost more than
-// the idle CUs (64 leaves 48 -> 45 us, ten trees of up to a few hundred leaves
-// 824 -> 778 us; a limit of 2000 took 2510 leaves from 139 to 163 us)
+// list-2 groups times right-hand sides up to which the compile-time M2L runs
+// one work-group per chunk of outputs: two groups per CU, beyond which the
+// chunks' repeated source loads cost more than the idle CUs.  Split and not, us
+// per execute: p = 24, 32 to 306 groups 69-97, 73-99; p = 40, 32 groups 92, 106;
+// 306: 129, 137; 344: 120, 127; 444: 141, 142; p = 30, 312: 103, 102; ten trees
+// of 160 to 976 leaves 778, 824; p = 24, 1313 groups (4207 leaves, with the
+// limit at 2000) 163, 139.
 constexpr long kM2LSplitGroups = 512;
 
 int launch_execute(Plan* p, int nrhs, const double* f_leaf, const double* f_cut, double* fe, double* V,

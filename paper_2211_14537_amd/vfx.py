@@ -335,8 +335,8 @@ class Plan:
                                             ctypes.c_void_p(st.cuda_stream)))
 
     def set_near_mode(self, mode):
-        """Near-field strategy (FP64, K = 16): 0 pair-based (default),
-        1 target-stationary."""
+        """Near-field strategy (FP64, K = 16): 0 from exterior moments
+        (default), 1 target-stationary."""
         _check(lib().vfx_plan_set_near_mode(self._h, int(mode)))
 
     def set_precision(self, mode, min_level=0):
